@@ -172,7 +172,9 @@ typedef struct {
 } mc_optics;
 
 /* Launch shape of the persistent walk.  Any value <= 0 selects the default.
- * Results do not depend on it. */
+ * Results do not depend on it.  With fewer photons than the shape has lanes, every
+ * wavefront takes its even share of them and no more lanes than that.  The walk in
+ * cells (mc_run_extra_workspace_bytes) has a shape of its own. */
 typedef struct {
     int32_t block;         /* threads per workgroup: 64, 128, 256, 512 */
     int32_t waves_per_cu;  /* resident waves per compute unit the grid is sized for */
@@ -191,12 +193,21 @@ void mc_tune_default(mc_tune *t);
 /* Workspace (device bytes) an mc_run on this volume needs. */
 size_t mc_run_workspace_bytes(const mc_volume *vol);
 
+/* Further workspace that makes an mc_run, mc_run_escape_histogram or mc_grad of n_photons on this
+ * volume faster: given at least mc_run_workspace_bytes(vol) (mc_grad_workspace_bytes(vol)) plus this,
+ * a large run walks its photons through the volume cell by cell with the tallies in LDS (1e8 photons
+ * at 256^3: 0.49 s against 1.26 s), the photons under way waiting in this workspace, 72 bytes each for
+ * up to 12.6e6 of them.  0 where it would not be used.  With less, fewer photons are under way at
+ * once, or the run takes the path that needs none; the results are the same bit for bit. */
+size_t mc_run_extra_workspace_bytes(const mc_volume *vol, uint64_t n_photons);
+
 /*
  * Run photons [photon_begin, photon_begin + n_photons) of the stream
  * (seed, stream_id) through the volume (Sec. 2.5, App. B).
  *   fluence  device int64[nz][ny][nx], Q31 weight x voxel (track-length estimator)
  *   scalars  device int64[MC_NSCALARS]
- *   workspace, workspace_bytes  device scratch of >= mc_run_workspace_bytes(vol)
+ *   workspace, workspace_bytes  device scratch of >= mc_run_workspace_bytes(vol); see
+ *            mc_run_extra_workspace_bytes for what a large run makes use of beyond that
  *   tune     launch shape, or NULL for defaults
  * Tallies are zeroed first unless flags has MC_ACCUMULATE.  Photon p draws
  * Philox4x32-10 block k (k = 0 launch, k >= 1 its k-th interaction) with

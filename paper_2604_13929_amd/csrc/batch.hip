@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "stage.hpp"
 
 using namespace pmc;
 using namespace pmc::host;
@@ -45,25 +46,8 @@ __global__ void k_write_jobs(JobPack pack, Job *__restrict__ dst, int32_t count)
     for (int32_t i = threadIdx.x; i < count * w; i += blockDim.x) d[i] = src[i];
 }
 
-// The escape-path histogram of one job (table order), NULL w: none.  Read only
-// when a photon escapes, so it stays in global memory, not in the LDS job table.
-// The walk adds into kEscReplicas copies in the workspace, a workgroup's copy
-// chosen by its index: a batch runs its jobs longest first, so at any time most
-// of the chip's escapes go to a few bins of one job, and one 64-byte line takes
-// only ~1e8 atomics per second at the memory side.  k_esc_fold adds the copies
-// into the caller's bins after the walk.
-constexpr int kEscReplicas = 16;
-struct BatchEsc {
-    unsigned long long *w;    // [nbins] escaped Q31 weight (the caller's)
-    unsigned long long *n;    // [nbins] escaped photons (the caller's)
-    unsigned long long *rw;   // [kEscReplicas][kEscMaxBins] copies of w (workspace)
-    unsigned long long *rn;   // [kEscReplicas][kEscMaxBins] copies of n (workspace)
-    double width;
-    int32_t nbins;
-    int32_t pad;
-};
 static_assert(sizeof(BatchEsc) % 8 == 0, "histogram table is written in 8-byte words");
-constexpr size_t kEscReplicaWords = 2ull * kEscReplicas * kEscMaxBins;   // per job: copies of w and n
+constexpr size_t kEscReplicaWords = 2ull * kEscReplicas * host::kEscMaxBins;   // per job: copies of w and n
 
 struct EscPack {
     BatchEsc e[16];
@@ -104,107 +88,6 @@ struct BatchTallySink {
     }
 };
 
-// Line-coalesced deposits for the batch: as the plain walk's log (8-byte
-// entries, 16 slots per lane, issued transposed once some lane has filled its
-// slots, the run of entries in the line a photon still deposits into held back,
-// uint32 staging words in each job's own layout, planes or lines, carries of
-// wrapped words into the job's int64 tally), with the job index in the top 6 bits
-// of the 32-bit entry index, which leaves 26 bits for the word index into the
-// job's staging tally (the batch logs only when every job's staging tally is that
-// small).  A deposit of 2^31 quanta or more goes to the job's tally directly.  The
-// log's 33 KB of LDS per 256-thread workgroup, with the job table and the per-job
-// channels, still lets three workgroups share a CU.
-constexpr int kBLogK = 16;
-constexpr int kBLogStride = 65;
-#ifndef MC_LOG_HOLD
-#define MC_LOG_HOLD 6
-#endif
-constexpr int kBLogHold = MC_LOG_HOLD;
-constexpr uint32_t kBNoLine = 0xFFFFFFFFu;
-constexpr int kJobShift = 26;
-constexpr uint32_t kIdxMask = (1u << kJobShift) - 1u;
-constexpr uint64_t kBatchLogWords = 1ull << kJobShift;   // largest staging tally a logged batch job may have
-
-struct BatchLoggedSink {
-    uint32_t *lidx;
-    uint32_t *lval;
-    uint32_t lane;
-    uint32_t head, count;       // this lane's ring of kBLogK slots
-    uint32_t tag;               // job << kJobShift
-    template <typename R> __device__ __forceinline__ void segment(const Photon<R> &, const Job &, R, bool) {}
-    template <typename R> __device__ __forceinline__ void deflect(Photon<R> &, const Job &, R) {}
-    template <typename R> __device__ __forceinline__ void flush(const Job &J, const Photon<R> &p, uint64_t a)
-    {
-        if (a != 0ull) {
-            if (a >> 31) {
-                __hip_atomic_fetch_add((unsigned long long *)(J.fluence + voxel_index(J, p)),
-                                       (unsigned long long)a << kDepositShift, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                const uint32_t s = log_slot<kBLogStride, kBLogK>(lane, head, count);
-                lidx[s] = stage_word(J, p) | tag;
-                lval[s] = (uint32_t)a;
-                ++count;
-            }
-        }
-    }
-};
-
-// Issue the wavefront's log; HOLD: the newest run of each lane's log that lies in
-// `line` (job bits included; kBNoLine: none) stays as the lane's ring.  The FP64
-// transport holds nothing.
-template <bool HOLD>
-__device__ __forceinline__ void flush_batch_log(uint32_t *lidx, uint32_t *lval, const Job *jobs, uint32_t lane,
-                                                uint32_t line, uint32_t &head, uint32_t &count)
-{
-    const uint32_t held = HOLD ? log_mark_run<kBLogStride, kBLogK, kBLogHold>(lidx, lval, lane, head, count, line) : 0u;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // in two halves, each issuing its adds before it looks at what they returned
-#pragma unroll
-    for (int h = 0; h < kBLogK; h += kBLogK / 2) {
-        uint32_t old[kBLogK / 2];
-#pragma unroll
-        for (int i = 0; i < kBLogK / 2; ++i) {
-            const uint32_t src = (uint32_t)(h + i) * (64 / kBLogK) + lane / kBLogK;
-            const uint32_t e = (lane % kBLogK) * kBLogStride + src;
-            const uint32_t v = lval[e];
-            old[i] = 0u;
-            if (v != 0u && (!HOLD || v < kLogHeld)) {
-                const uint32_t w = lidx[e];
-                old[i] = __hip_atomic_fetch_add(jobs[w >> kJobShift].stage + (w & kIdxMask), v, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kBLogK / 2; ++i) {
-            const uint32_t src = (uint32_t)(h + i) * (64 / kBLogK) + lane / kBLogK;
-            const uint32_t e = (lane % kBLogK) * kBLogStride + src;
-            const uint32_t v = lval[e];
-            if (v != 0u && (!HOLD || v < kLogHeld)) {
-                if (old[i] > 0xFFFFFFFFu - v) {
-                    // the word wrapped: its lost 2^32 quanta go to the voxel's int64 word
-                    const uint32_t w = lidx[e];
-                    const Job &J = jobs[w >> kJobShift];
-                    __hip_atomic_fetch_add((unsigned long long *)(J.fluence + stage_voxel(J, w & kIdxMask)),
-                                           1ull << (32 + kDepositShift), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                lval[e] = 0u;
-            }
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (HOLD) {
-        log_keep_run<kBLogStride, kBLogK, kBLogHold>(lval, lane, head, count, held);
-    } else {
-        head = 0u;
-        count = 0u;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <typename R>
 __device__ __forceinline__ void account_job(unsigned long long *acc, const Photon<R> &p, int32_t ev, int32_t nz)
 {
@@ -240,8 +123,8 @@ __device__ __forceinline__ void account_job(unsigned long long *acc, const Photo
 // physics).  esc: per-job escape-path histograms (Sec. 3.5 (c)), or NULL.
 template <int BLOCK, typename R, bool LOGGED, bool GENERAL>
 __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jobs, int32_t n_jobs,
-                                                      unsigned long long *__restrict__ queue, int32_t chunk,
-                                                      int32_t refill, int32_t defer,
+                                                      unsigned long long *__restrict__ queue, int32_t cap,
+                                                      int32_t chunk, int32_t refill, int32_t defer,
                                                       const BatchEsc *__restrict__ esc)
 {
     constexpr int kWaves = BLOCK / 64;
@@ -298,8 +181,8 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
     for (;;) {
         const uint64_t idle = __ballot(!alive);
         if (idle != 0ull) {
-            const int32_t nidle = __popcll(idle);
-            if (!exhausted && (nidle >= refill || idle == ~0ull)) {
+            const int32_t room = cap - (64 - (int32_t)__popcll(idle));
+            if (!exhausted && (room >= refill || idle == ~0ull)) {
                 if (q_next >= q_end) {
                     unsigned long long base = 0ull;
                     if (lane == 0) base = atomicAdd(queue, (unsigned long long)chunk);
@@ -314,7 +197,7 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
                 if (q_next < q_end) {
                     const uint64_t avail = q_end - q_next;
                     const uint32_t rank = (uint32_t)__popcll(idle & __lanemask_lt());
-                    if (!alive && rank < avail) {
+                    if (!alive && (int32_t)rank < room && rank < avail) {
                         const uint64_t q = q_next + rank;
                         int32_t lo = 0, hi = n_jobs - 1;  // last job whose range starts at or before q
                         while (lo < hi) {
@@ -327,7 +210,7 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
                         launch<GENERAL>(p, J, (uint32_t)(J.photon_begin + (q - J.queue_begin)));
                         alive = true;
                     }
-                    q_next += (uint64_t)nidle < avail ? (uint64_t)nidle : avail;
+                    q_next += (uint64_t)room < avail ? (uint64_t)room : avail;
                 }
             }
             if (exhausted && q_next >= q_end && !__any(alive)) break;
@@ -471,24 +354,24 @@ int prepare(const mc_job *jobs, int32_t n, char *ws, size_t ws_bytes, int flags,
 
 template <typename R, bool LOGGED, bool GENERAL>
 void enqueue_batch_walk(int block, int blocks, const Job *table, int32_t n, unsigned long long *queue,
-                        const mc_tune &t, const BatchEsc *esc, hipStream_t s)
+                        const WalkShape &sh, const BatchEsc *esc, hipStream_t s)
 {
     switch (block) {
     case 64:
-        hipLaunchKernelGGL((k_walk_batch<64, R, LOGGED, GENERAL>), dim3(blocks), dim3(64), 0, s, table, n, queue, t.chunk,
-                           t.refill, t.defer, esc);
+        hipLaunchKernelGGL((k_walk_batch<64, R, LOGGED, GENERAL>), dim3(blocks), dim3(64), 0, s, table, n, queue, sh.cap,
+                           sh.chunk, sh.refill, sh.defer, esc);
         break;
     case 128:
-        hipLaunchKernelGGL((k_walk_batch<128, R, LOGGED, GENERAL>), dim3(blocks), dim3(128), 0, s, table, n, queue, t.chunk,
-                           t.refill, t.defer, esc);
+        hipLaunchKernelGGL((k_walk_batch<128, R, LOGGED, GENERAL>), dim3(blocks), dim3(128), 0, s, table, n, queue, sh.cap,
+                           sh.chunk, sh.refill, sh.defer, esc);
         break;
     case 256:
-        hipLaunchKernelGGL((k_walk_batch<256, R, LOGGED, GENERAL>), dim3(blocks), dim3(256), 0, s, table, n, queue, t.chunk,
-                           t.refill, t.defer, esc);
+        hipLaunchKernelGGL((k_walk_batch<256, R, LOGGED, GENERAL>), dim3(blocks), dim3(256), 0, s, table, n, queue, sh.cap,
+                           sh.chunk, sh.refill, sh.defer, esc);
         break;
     default:
-        hipLaunchKernelGGL((k_walk_batch<512, R, LOGGED, GENERAL>), dim3(blocks), dim3(512), 0, s, table, n, queue, t.chunk,
-                           t.refill, t.defer, esc);
+        hipLaunchKernelGGL((k_walk_batch<512, R, LOGGED, GENERAL>), dim3(blocks), dim3(512), 0, s, table, n, queue, sh.cap,
+                           sh.chunk, sh.refill, sh.defer, esc);
         break;
     }
 }
@@ -517,6 +400,7 @@ int enqueue_walk_only(const Prepared &P, char *ws, const mc_tune &t, int flags, 
     if (rc) return rc;
     if ((rc = fill((int64_t *)ws, kHeaderBytes / 8, s))) return rc;
     const int blocks = std::max(1, di.cus * t.waves_per_cu / (t.block / 64));
+    const WalkShape sh = walk_shape(t, (uint64_t)blocks * (uint64_t)(t.block / 64), P.total_photons);
     const Job *table = (const Job *)(ws + P.L.jobs_off);
     const BatchEsc *esc = with_esc ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr;
     unsigned long long *queue = (unsigned long long *)ws;
@@ -524,19 +408,19 @@ int enqueue_walk_only(const Prepared &P, char *ws, const mc_tune &t, int flags, 
     const bool f64 = (flags & MC_FP64) != 0;
     if (P.general) {
         if (P.L.logged) {
-            if (f64) enqueue_batch_walk<double, true, true>(t.block, blocks, table, n, queue, t, esc, s);
-            else enqueue_batch_walk<float, true, true>(t.block, blocks, table, n, queue, t, esc, s);
+            if (f64) enqueue_batch_walk<double, true, true>(t.block, blocks, table, n, queue, sh, esc, s);
+            else enqueue_batch_walk<float, true, true>(t.block, blocks, table, n, queue, sh, esc, s);
         } else {
-            if (f64) enqueue_batch_walk<double, false, true>(t.block, blocks, table, n, queue, t, esc, s);
-            else enqueue_batch_walk<float, false, true>(t.block, blocks, table, n, queue, t, esc, s);
+            if (f64) enqueue_batch_walk<double, false, true>(t.block, blocks, table, n, queue, sh, esc, s);
+            else enqueue_batch_walk<float, false, true>(t.block, blocks, table, n, queue, sh, esc, s);
         }
     } else {
         if (P.L.logged) {
-            if (f64) enqueue_batch_walk<double, true, false>(t.block, blocks, table, n, queue, t, esc, s);
-            else enqueue_batch_walk<float, true, false>(t.block, blocks, table, n, queue, t, esc, s);
+            if (f64) enqueue_batch_walk<double, true, false>(t.block, blocks, table, n, queue, sh, esc, s);
+            else enqueue_batch_walk<float, true, false>(t.block, blocks, table, n, queue, sh, esc, s);
         } else {
-            if (f64) enqueue_batch_walk<double, false, false>(t.block, blocks, table, n, queue, t, esc, s);
-            else enqueue_batch_walk<float, false, false>(t.block, blocks, table, n, queue, t, esc, s);
+            if (f64) enqueue_batch_walk<double, false, false>(t.block, blocks, table, n, queue, sh, esc, s);
+            else enqueue_batch_walk<float, false, false>(t.block, blocks, table, n, queue, sh, esc, s);
         }
     }
     HIP_TRY(hipGetLastError());
@@ -546,28 +430,22 @@ int enqueue_walk_only(const Prepared &P, char *ws, const mc_tune &t, int flags, 
 // The histogram table in queue order, from the caller's per-job bins (validated).
 int enqueue_esc_table(const Prepared &P, const mc_escape_bins *bins, char *ws, hipStream_t s)
 {
-    BatchEsc *dst = (BatchEsc *)(ws + P.L.esc_off);
+    BatchEsc e[MC_MAX_BATCH_JOBS];
+    memset(e, 0, sizeof e);
     const int32_t n = (int32_t)P.table.size();
-    for (int32_t i = 0; i < n; i += 16) {
-        EscPack pack;
-        memset(&pack, 0, sizeof pack);
-        const int32_t c = std::min(16, n - i);
-        for (int32_t k = 0; k < c; ++k) {
-            const int32_t job = P.order[i + k];
-            const mc_escape_bins &b = bins[job];
-            if (!b.hist_w) continue;
-            unsigned long long *rep = (unsigned long long *)(ws + P.L.esc_rep_off[job]);
-            pack.e[k].w = (unsigned long long *)b.hist_w;
-            pack.e[k].n = (unsigned long long *)b.hist_n;
-            pack.e[k].rw = rep;
-            pack.e[k].rn = rep + (size_t)kEscReplicas * kEscMaxBins;
-            pack.e[k].width = b.bin_width;
-            pack.e[k].nbins = b.nbins;
-        }
-        hipLaunchKernelGGL(k_write_esc, dim3(1), dim3(256), 0, s, pack, dst + i, c);
-        HIP_TRY(hipGetLastError());
+    for (int32_t k = 0; k < n; ++k) {
+        const int32_t job = P.order[k];
+        const mc_escape_bins &b = bins[job];
+        if (!b.hist_w) continue;
+        unsigned long long *rep = (unsigned long long *)(ws + P.L.esc_rep_off[job]);
+        e[k].w = (unsigned long long *)b.hist_w;
+        e[k].n = (unsigned long long *)b.hist_n;
+        e[k].rw = rep;
+        e[k].rn = rep + (size_t)kEscReplicas * kEscMaxBins;
+        e[k].width = b.bin_width;
+        e[k].nbins = b.nbins;
     }
-    return MC_OK;
+    return write_esc(e, n, (BatchEsc *)(ws + P.L.esc_off), s);
 }
 
 // The whole batched step: table, zeroed tallies, packed masks, one walk, reductions.
@@ -606,8 +484,7 @@ int enqueue_batch(const mc_job *jobs, const Prepared &P, char *ws, const mc_tune
     if ((rc = enqueue_walk_only(P, ws, t, flags, s, bins != nullptr))) return rc;
     if (timed && (rc = time_end(s))) return rc;
     if (bins) {
-        hipLaunchKernelGGL(k_esc_fold, dim3(n), dim3(256), 0, s, (const BatchEsc *)(ws + P.L.esc_off));
-        HIP_TRY(hipGetLastError());
+        if ((rc = fold_esc((const BatchEsc *)(ws + P.L.esc_off), n, s))) return rc;
     }
     if (P.L.logged) {
         for (int32_t i = 0; i < n; ++i) {
@@ -817,6 +694,32 @@ struct GraphHandle {
 };
 
 }  // namespace
+
+namespace pmc {
+namespace host {
+
+int write_esc(const BatchEsc *e, int32_t n, BatchEsc *dst, hipStream_t s)
+{
+    for (int32_t i = 0; i < n; i += 16) {
+        EscPack pack;
+        memset(&pack, 0, sizeof pack);
+        const int32_t c = std::min(16, n - i);
+        for (int32_t k = 0; k < c; ++k) pack.e[k] = e[i + k];
+        hipLaunchKernelGGL(k_write_esc, dim3(1), dim3(256), 0, s, pack, dst + i, c);
+        HIP_TRY(hipGetLastError());
+    }
+    return MC_OK;
+}
+
+int fold_esc(const BatchEsc *table, int32_t n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_esc_fold, dim3(n), dim3(256), 0, s, table);
+    HIP_TRY(hipGetLastError());
+    return MC_OK;
+}
+
+}  // namespace host
+}  // namespace pmc
 
 // ---------------------------------------------------------------------------
 // C ABI

@@ -9,6 +9,25 @@
 struct EscHist;  // the escape-path histogram of a walk (photonmc.hip)
 
 namespace pmc {
+
+// The escape-path histogram of one job (table order), NULL w: none.  Read only
+// when a photon escapes, so it stays in global memory, not in the LDS job table.
+// The walk adds into kEscReplicas copies in the workspace, a workgroup's copy
+// chosen by its index: a batch runs its jobs longest first, so at any time most
+// of the chip's escapes go to a few bins of one job, and one 64-byte line takes
+// only ~1e8 atomics per second at the memory side.  k_esc_fold adds the copies
+// into the caller's bins after the walk.
+constexpr int kEscReplicas = 16;
+struct BatchEsc {
+    unsigned long long *w;    // [nbins] escaped Q31 weight (the caller's)
+    unsigned long long *n;    // [nbins] escaped photons (the caller's)
+    unsigned long long *rw;   // [kEscReplicas][kEscMaxBins] copies of w (workspace)
+    unsigned long long *rn;   // [kEscReplicas][kEscMaxBins] copies of n (workspace)
+    double width;
+    int32_t nbins;
+    int32_t pad;
+};
+
 namespace host {
 
 int fail(int status, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
@@ -60,6 +79,14 @@ mc_tune resolve_tune(const mc_tune *t, int32_t defer_default = 0);
 // transport are bound by their VALU and run their interactions in larger groups.
 constexpr int32_t kDeferVALUBound = 8;
 int check_tune(const mc_tune &t);
+// What a walk of so many wavefronts does with a tune for so many photons.  With fewer photons than
+// lanes every wavefront takes its even share and no more lanes than that: a wavefront of one photon
+// steps in 0.7 us, one of 64 in 1.3 to 3 us, and the run lasts as long as its longest photon.  Few
+// lanes also wait less for each other's interactions.
+struct WalkShape {
+    int32_t cap, chunk, refill, defer;
+};
+WalkShape walk_shape(const mc_tune &t, uint64_t waves, uint64_t photons);
 
 // asynchronous building blocks on a stream
 int fill(int64_t *p, uint64_t n, hipStream_t s);
@@ -67,8 +94,12 @@ int pack(const mc_volume *vol, uint64_t *bricks, hipStream_t s);
 int unstage(const uint32_t *stage, int64_t *fluence, const mc_volume *vol, bool planes, hipStream_t s);
 // zero (unless accumulating), pack, walk and move the staged tally into the caller's
 // fluence, with the queue, packed mask and staging tally in the workspace ws
-int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws, unsigned long long *grad_bins,
-             hipStream_t s, const EscHist *esc = nullptr);
+// (cells, cells_bytes: scratch of the cell walk, or NULL)
+int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws, char *cells, size_t cells_bytes,
+             unsigned long long *grad_bins, hipStream_t s, const EscHist *esc = nullptr);
+// the histogram table's entries from the host, and the copies added into the callers' bins
+int write_esc(const BatchEsc *e, int32_t n, BatchEsc *dst, hipStream_t s);
+int fold_esc(const BatchEsc *table, int32_t n, hipStream_t s);
 int enqueue_reduce(const mc_volume *vol, const int64_t *fluence, const int64_t *scalars, double *summary,
                    double *depth, unsigned long long *bins, hipStream_t s);
 

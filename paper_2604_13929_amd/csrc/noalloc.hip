@@ -68,7 +68,7 @@ int mc_run_noalloc(const mc_volume *vol, const mc_optics *opt, uint64_t photon_b
     J.scalars = scalars;
     // the queue counter and the packed mask sit where mc_run's workspace holds them;
     // MC_DIRECT_DEPOSIT leaves the staging tally out, so they are all the walk uses
-    return run_walk(vol, J, flags | MC_DIRECT_DEPOSIT, t, (char *)ws, nullptr, (hipStream_t)hip_stream);
+    return run_walk(vol, J, flags | MC_DIRECT_DEPOSIT, t, (char *)ws, nullptr, 0, nullptr, (hipStream_t)hip_stream);
 }
 
 }  // extern "C"

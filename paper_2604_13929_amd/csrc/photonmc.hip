@@ -20,7 +20,9 @@
 #include <algorithm>
 #include <mutex>
 
+#include "cells.hpp"
 #include "internal.hpp"
+#include "score.hpp"
 #include "spinodal.h"
 
 using namespace pmc;
@@ -245,56 +247,6 @@ struct TallySink : Deposit {
     template <typename R> __device__ __forceinline__ void deflect(Photon<R> &, const Job &, R) {}
 };
 
-// Likelihood-ratio (perturbation Monte Carlo) scores of the track-length
-// estimator.  The sampled path density is mu_s^k exp(-mu_t l_solid) prod p_HG;
-// its log-derivatives give the scores S_mus = k/mu_s - l_solid,
-// S_mua = -l_solid and S_g = sum_i d ln p_HG(cos_i)/dg.  A segment of length d
-// starting with those scores adds w (S d - [solid] d^2/2) to the mu_s and mu_a
-// bins (the d^2/2 is the survival inside the segment) and w S_g d to the g bin,
-// per (parameter, phase, depth), in fixed point 2^-MC_GRAD_FIXED_BITS of a Q31
-// weight x voxel, each segment's value rounded to nearest.  Roulette decisions
-// carry no score: survival 1/m with weight x m is unbiased.
-constexpr double kGradScale = 1.0 / (double)(1ll << MC_GRAD_FIXED_BITS);
-
-// The block keeps its score bins in LDS as int32 words (half the space of int64
-// bins: four 256-thread walk workgroups still fit per CU at nz = 256) and moves a
-// word to the global (hi, lo) int64 pairs before it can overflow.  A value of
-// magnitude >= kGradDirect goes to the global pair directly; any other is added
-// to its word, and a lane whose add leaves the word at magnitude >= kGradSpill
-// swaps the word for 0 and adds what it took to the global pair.  A lane that
-// sees the threshold swaps before its next add, so at most one add per thread of
-// the block lands on a word between its crossing and the swap: |word| < kGradSpill
-// + 512 * kGradDirect = 2^28 + 2^30.  Every transfer is exact, so the totals are
-// the integer sums of the segments' fixed-point values whatever the order.  The
-// global pairs are few (6 nz, a hot address each), so the direct path must stay
-// rare: at 2^-20 a value reaches 2^21 only where (w / 2^31) |S| d reaches 1024
-// voxels, while under implicit capture (w / 2^31) l_solid peaks at 1 / (e mu_a),
-// 37 voxels at mu_a = 0.01.
-constexpr long long kGradDirect = 1ll << 21;
-constexpr int kGradSpill = 1 << 28;
-
-__device__ __forceinline__ void grad_global_add(unsigned long long *grad, int32_t i, long long v)
-{
-    atomicAdd(&grad[2 * i], (unsigned long long)(v >> 32));
-    atomicAdd(&grad[2 * i + 1], (unsigned long long)v & 0xFFFFFFFFull);
-}
-
-__device__ __forceinline__ void grad_bin_add(int *bins, unsigned long long *grad, int32_t i, long long v)
-{
-    if (v == 0) return;
-    if (v >= kGradDirect || v <= -kGradDirect) {
-        grad_global_add(grad, i, v);
-        return;
-    }
-    const long long nv = (long long)atomicAdd(&bins[i], (int)v) + v;
-    if (nv >= kGradSpill || nv <= -kGradSpill) grad_global_add(grad, i, (long long)atomicExch(&bins[i], 0));
-}
-
-__device__ __forceinline__ double hg_score(double ct, double g)
-{
-    return -2.0 * g / (1.0 - g * g) + 3.0 * (ct - g) / (1.0 + g * g - 2.0 * g * ct);
-}
-
 template <class Deposit>
 struct GradSink : Deposit {
     int *bins;                 // LDS [3][2][nz] int32 words
@@ -305,13 +257,9 @@ struct GradSink : Deposit {
     __device__ __forceinline__ void segment(const Photon<R> &p, const Job &, R d, bool solid)
     {
         if (p.iz < 0 || p.iz >= nz) return;                  // air pads carry no bins
-        const double dd = (double)d, ls = p.l_tot - p.l_void;  // solid path before this segment
-        const double sq = solid ? 0.5 * dd * dd : 0.0;
-        const double sw = (double)p.w * kGradScale;
+        long long vs, va, vg;
+        grad_values(p, inv_mu_s, (double)d, solid, vs, va, vg);
         const int32_t base = (solid ? 0 : nz) + p.iz;
-        const long long vs = __double2ll_rn(sw * (((double)p.k * inv_mu_s - ls) * dd - sq));
-        const long long va = __double2ll_rn(sw * (-ls * dd - sq));
-        const long long vg = __double2ll_rn(sw * (p.score_g * dd));
         grad_bin_add(bins, grad, base, vs);
         grad_bin_add(bins, grad, 2 * nz + base, va);
         grad_bin_add(bins, grad, 4 * nz + base, vg);
@@ -363,9 +311,10 @@ struct EscHist {
 // Persistent walk
 // ---------------------------------------------------------------------------
 // Each wavefront owns a private range [q_next, q_end) of queue positions and
-// takes `chunk` more with one atomic when it runs dry.  Idle lanes are refilled
-// together once at least `refill` of them are idle (or all are), so launches
-// run converged.  A lane whose segment ends at an interaction point waits there
+// takes `chunk` more with one atomic when it runs dry.  It uses at most `cap`
+// lanes (fewer than 64 where there are fewer photons than lanes on the chip, so
+// that they spread over all wavefronts).  Idle lanes are refilled together once
+// at least `refill` of them are idle (or all are), so launches run converged.  A lane whose segment ends at an interaction point waits there
 // until `defer` lanes of its wavefront wait (or no lane can advance); then the
 // waiting lanes run their interactions together, so that code runs with many
 // lanes active instead of a few in every iteration.  A photon's own sequence of
@@ -382,8 +331,9 @@ template <bool GRAD, bool LOGGED> struct SinkOf {
 // step that also knows the paper's boundary model (see walk.hpp).
 // ESC: also bin the in-pore path of every escaping photon (EscHist).
 template <int BLOCK, typename R, bool GRAD, bool LOGGED, bool GENERAL, bool ESC>
-__global__ __launch_bounds__(BLOCK) void k_walk(const Job J, unsigned long long *__restrict__ queue, int32_t chunk,
-                                                int32_t refill, int32_t defer, unsigned long long *__restrict__ grad,
+__global__ __launch_bounds__(BLOCK) void k_walk(const Job J, unsigned long long *__restrict__ queue, int32_t cap,
+                                                int32_t chunk, int32_t refill, int32_t defer,
+                                                unsigned long long *__restrict__ grad,
                                                 const EscHist eh)
 {
     constexpr int kWaves = BLOCK / 64;
@@ -445,8 +395,8 @@ __global__ __launch_bounds__(BLOCK) void k_walk(const Job J, unsigned long long 
     for (;;) {
         const uint64_t idle = __ballot(!alive);
         if (idle != 0ull) {
-            const int32_t nidle = __popcll(idle);
-            if (!exhausted && (nidle >= refill || idle == ~0ull)) {
+            const int32_t room = cap - (64 - (int32_t)__popcll(idle));
+            if (!exhausted && (room >= refill || idle == ~0ull)) {
                 if (q_next >= q_end) {
                     unsigned long long base = 0ull;
                     if (lane == 0) base = atomicAdd(queue, (unsigned long long)chunk);
@@ -461,11 +411,11 @@ __global__ __launch_bounds__(BLOCK) void k_walk(const Job J, unsigned long long 
                 if (q_next < q_end) {
                     const uint64_t avail = q_end - q_next;
                     const uint32_t rank = (uint32_t)__popcll(idle & __lanemask_lt());
-                    if (!alive && rank < avail) {
+                    if (!alive && (int32_t)rank < room && rank < avail) {
                         launch<GENERAL>(p, J, (uint32_t)(J.photon_begin + q_next + rank));
                         alive = true;
                     }
-                    q_next += (uint64_t)nidle < avail ? (uint64_t)nidle : avail;
+                    q_next += (uint64_t)room < avail ? (uint64_t)room : avail;
                 }
             }
             if (exhausted && q_next >= q_end && !__any(alive)) break;
@@ -984,6 +934,17 @@ mc_tune resolve_tune(const mc_tune *t, int32_t defer_default)
     return r;
 }
 
+WalkShape walk_shape(const mc_tune &t, uint64_t waves, uint64_t photons)
+{
+    const uint64_t share = std::max<uint64_t>(1, (photons + waves - 1) / waves);
+    WalkShape s;
+    s.cap = (int32_t)std::min<uint64_t>(64, share);
+    s.chunk = (int32_t)std::min<uint64_t>((uint64_t)t.chunk, share);
+    s.refill = std::min(t.refill, s.cap);
+    s.defer = std::min(t.defer, std::max(1, s.cap / 8));
+    return s;
+}
+
 int check_tune(const mc_tune &t)
 {
     if (t.block != 64 && t.block != 128 && t.block != 256 && t.block != 512)
@@ -1052,41 +1013,41 @@ int enqueue_reduce(const mc_volume *vol, const int64_t *fluence, const int64_t *
 }
 
 template <typename R, bool GRAD, bool LOGGED, bool GENERAL, bool ESC>
-void enqueue_walk(int block, int blocks, const Job &J, unsigned long long *queue, const mc_tune &t,
+void enqueue_walk(int block, int blocks, const Job &J, unsigned long long *queue, const WalkShape &sh,
                   unsigned long long *grad, const EscHist &eh, hipStream_t s)
 {
     const size_t lds = GRAD ? (size_t)6 * J.nz * sizeof(int)
                             : (ESC ? (size_t)eh.nbins * (sizeof(unsigned long long) + sizeof(unsigned int)) : 0);
     switch (block) {
     case 64:
-        hipLaunchKernelGGL((k_walk<64, R, GRAD, LOGGED, GENERAL, ESC>), dim3(blocks), dim3(64), lds, s, J, queue, t.chunk,
-                           t.refill, t.defer, grad, eh);
+        hipLaunchKernelGGL((k_walk<64, R, GRAD, LOGGED, GENERAL, ESC>), dim3(blocks), dim3(64), lds, s, J, queue, sh.cap,
+                           sh.chunk, sh.refill, sh.defer, grad, eh);
         break;
     case 128:
         hipLaunchKernelGGL((k_walk<128, R, GRAD, LOGGED, GENERAL, ESC>), dim3(blocks), dim3(128), lds, s, J, queue,
-                           t.chunk, t.refill, t.defer, grad, eh);
+                           sh.cap, sh.chunk, sh.refill, sh.defer, grad, eh);
         break;
     case 256:
         hipLaunchKernelGGL((k_walk<256, R, GRAD, LOGGED, GENERAL, ESC>), dim3(blocks), dim3(256), lds, s, J, queue,
-                           t.chunk, t.refill, t.defer, grad, eh);
+                           sh.cap, sh.chunk, sh.refill, sh.defer, grad, eh);
         break;
     default:
         hipLaunchKernelGGL((k_walk<512, R, GRAD, LOGGED, GENERAL, ESC>), dim3(blocks), dim3(512), lds, s, J, queue,
-                           t.chunk, t.refill, t.defer, grad, eh);
+                           sh.cap, sh.chunk, sh.refill, sh.defer, grad, eh);
         break;
     }
 }
 
 template <typename R, bool GRAD, bool ESC>
-void enqueue_walk_dep(bool logged, int block, int blocks, const Job &J, unsigned long long *queue, const mc_tune &t,
+void enqueue_walk_dep(bool logged, int block, int blocks, const Job &J, unsigned long long *queue, const WalkShape &sh,
                       unsigned long long *grad, const EscHist &eh, hipStream_t s)
 {
     if (J.paper) {
-        if (logged) enqueue_walk<R, GRAD, true, true, ESC>(block, blocks, J, queue, t, grad, eh, s);
-        else enqueue_walk<R, GRAD, false, true, ESC>(block, blocks, J, queue, t, grad, eh, s);
+        if (logged) enqueue_walk<R, GRAD, true, true, ESC>(block, blocks, J, queue, sh, grad, eh, s);
+        else enqueue_walk<R, GRAD, false, true, ESC>(block, blocks, J, queue, sh, grad, eh, s);
     } else {
-        if (logged) enqueue_walk<R, GRAD, true, false, ESC>(block, blocks, J, queue, t, grad, eh, s);
-        else enqueue_walk<R, GRAD, false, false, ESC>(block, blocks, J, queue, t, grad, eh, s);
+        if (logged) enqueue_walk<R, GRAD, true, false, ESC>(block, blocks, J, queue, sh, grad, eh, s);
+        else enqueue_walk<R, GRAD, false, false, ESC>(block, blocks, J, queue, sh, grad, eh, s);
     }
 }
 
@@ -1098,18 +1059,19 @@ int launch_walk(const Job &J, unsigned long long *queue, const mc_tune &t, hipSt
     if (rc) return rc;
     const int waves_per_block = t.block / 64;
     const int blocks = std::max(1, di.cus * t.waves_per_cu / waves_per_block);
+    const WalkShape sh = walk_shape(t, (uint64_t)blocks * waves_per_block, J.n_photons);
     const bool timed = (flags & MC_TIMED) != 0;
     if (timed && (rc = time_begin(s))) return rc;
     const EscHist none = {nullptr, nullptr, 1.0, 0};
     if (grad) {
-        if (flags & MC_FP64) enqueue_walk_dep<double, true, false>(logged, t.block, blocks, J, queue, t, grad, none, s);
-        else enqueue_walk_dep<float, true, false>(logged, t.block, blocks, J, queue, t, grad, none, s);
+        if (flags & MC_FP64) enqueue_walk_dep<double, true, false>(logged, t.block, blocks, J, queue, sh, grad, none, s);
+        else enqueue_walk_dep<float, true, false>(logged, t.block, blocks, J, queue, sh, grad, none, s);
     } else if (esc) {
-        if (flags & MC_FP64) enqueue_walk_dep<double, false, true>(logged, t.block, blocks, J, queue, t, nullptr, *esc, s);
-        else enqueue_walk_dep<float, false, true>(logged, t.block, blocks, J, queue, t, nullptr, *esc, s);
+        if (flags & MC_FP64) enqueue_walk_dep<double, false, true>(logged, t.block, blocks, J, queue, sh, nullptr, *esc, s);
+        else enqueue_walk_dep<float, false, true>(logged, t.block, blocks, J, queue, sh, nullptr, *esc, s);
     } else {
-        if (flags & MC_FP64) enqueue_walk_dep<double, false, false>(logged, t.block, blocks, J, queue, t, nullptr, none, s);
-        else enqueue_walk_dep<float, false, false>(logged, t.block, blocks, J, queue, t, nullptr, none, s);
+        if (flags & MC_FP64) enqueue_walk_dep<double, false, false>(logged, t.block, blocks, J, queue, sh, nullptr, none, s);
+        else enqueue_walk_dep<float, false, false>(logged, t.block, blocks, J, queue, sh, nullptr, none, s);
     }
     HIP_TRY(hipGetLastError());
     if (timed && (rc = time_end(s))) return rc;
@@ -1118,8 +1080,8 @@ int launch_walk(const Job &J, unsigned long long *queue, const mc_tune &t, hipSt
 
 // Zero the tallies (unless accumulating), pack the mask, walk, and for the
 // logged deposit path add the staged quanta to the caller's tally.
-int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws, unsigned long long *grad_bins,
-             hipStream_t s, const EscHist *esc)
+int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws, char *cells, size_t cells_bytes,
+             unsigned long long *grad_bins, hipStream_t s, const EscHist *esc)
 {
     const Dims d = dims_of(vol);
     const bool logged = d.logged && !(flags & MC_DIRECT_DEPOSIT);
@@ -1142,6 +1104,18 @@ int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws,
     J.bricks = bricks;
     J.stage = logged ? stage : nullptr;
     J.stage_planes = logged && planes;
+    if (logged && cells && !(flags & MC_LINE_STAGING)) {
+        const BatchEsc hist = esc ? BatchEsc{esc->w, esc->n, nullptr, nullptr, esc->width, esc->nbins, 0} : BatchEsc{};
+        const CellRun r = {&J, 1, J.n_photons, J.paper != 0, (flags & MC_FP64) != 0, grad_bins, nullptr,
+                           esc ? &hist : nullptr, cells, cells_bytes};
+        if (cell_walk_fits(r)) {
+            const bool timed = (flags & MC_TIMED) != 0;
+            if (timed && (rc = time_begin(s))) return rc;
+            if ((rc = cell_walk(r, s))) return rc;
+            if (timed && (rc = time_end(s))) return rc;
+            return unstage(stage, J.fluence, vol, planes, s);
+        }
+    }
     if ((rc = launch_walk(J, queue, t, s, flags, grad_bins, logged, esc))) return rc;
     if (logged) return unstage(stage, J.fluence, vol, planes, s);
     return MC_OK;
@@ -1212,6 +1186,13 @@ size_t mc_run_workspace_bytes(const mc_volume *vol)
     return run_workspace_bytes(dims_of(vol));
 }
 
+size_t mc_run_extra_workspace_bytes(const mc_volume *vol, uint64_t n_photons)
+{
+    if (check_volume(vol)) return 0;
+    const CellDims c = cell_dims(vol, true);
+    return cell_workspace_bytes(&c, 1, n_photons);
+}
+
 int mc_run(const mc_volume *vol, const mc_optics *opt, uint64_t photon_begin, uint64_t n_photons, uint64_t seed,
            uint32_t stream_id, int flags, int64_t *fluence, int64_t *scalars, void *workspace, size_t workspace_bytes,
            const mc_tune *tune, void *hip_stream)
@@ -1227,7 +1208,8 @@ int mc_run(const mc_volume *vol, const mc_optics *opt, uint64_t photon_begin, ui
     if ((rc = check_tune(t))) return rc;
     J.fluence = fluence;
     J.scalars = scalars;
-    return run_walk(vol, J, flags, t, (char *)workspace, nullptr, (hipStream_t)hip_stream);
+    return run_walk(vol, J, flags, t, (char *)workspace, (char *)workspace + need, workspace_bytes - need, nullptr,
+                    (hipStream_t)hip_stream);
 }
 
 int mc_run_escape_histogram(const mc_volume *vol, const mc_optics *opt, uint64_t photon_begin, uint64_t n_photons,
@@ -1250,7 +1232,8 @@ int mc_run_escape_histogram(const mc_volume *vol, const mc_optics *opt, uint64_t
     J.fluence = fluence;
     J.scalars = scalars;
     const EscHist esc = {(unsigned long long *)hist_w, (unsigned long long *)hist_n, bin_width, nbins};
-    return run_walk(vol, J, flags, t, (char *)workspace, nullptr, (hipStream_t)hip_stream, &esc);
+    return run_walk(vol, J, flags, t, (char *)workspace, (char *)workspace + need, workspace_bytes - need, nullptr,
+                    (hipStream_t)hip_stream, &esc);
 }
 
 int mc_walk_elapsed_ms(float *ms)
@@ -1342,7 +1325,7 @@ int mc_grad(const mc_volume *vol, const mc_optics *opt, uint64_t photon_begin, u
     double *scratch_q = (double *)(ws + mc_run_workspace_bytes(vol) + mc_reduce_workspace_bytes(vol));
     J.fluence = fluence;
     J.scalars = scalars;
-    if ((rc = run_walk(vol, J, flags, t, ws, (unsigned long long *)grad_bins, s))) return rc;
+    if ((rc = run_walk(vol, J, flags, t, ws, ws + need, workspace_bytes - need, (unsigned long long *)grad_bins, s))) return rc;
     if (jac || summary || depth) {
         if ((rc = enqueue_reduce(vol, fluence, scalars, summary ? summary : scratch_q, depth, bins, s))) return rc;
     }

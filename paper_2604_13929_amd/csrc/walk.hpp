@@ -94,10 +94,12 @@ struct Job {
 
 template <typename R>
 struct Photon {
+    using Real = R;
     int32_t ix, iy, iz;
     R fx, fy, fz;
     R ux, uy, uz;
     R iux, iuy, iuz;          // 1/|u| per axis (+inf where u = 0), kept with the direction
+    R bx, by, bz;             // offset of the face ahead per axis: 1 where u > 0, else 0
     double s_rem;             // remaining free path, in solid path length
     double l_void, l_tot;     // path inside pores, total path
     double score_g;           // sum of d ln p_HG / dg over the deflections so far (gradient walk)
@@ -131,8 +133,6 @@ __device__ __forceinline__ void r_sincos_turn(double u, double *s, double *c) { 
 // ln u for u in (0, 1]
 __device__ __forceinline__ float r_log_unit(float u) { return __builtin_amdgcn_logf(u) * 0.693147180559945309f; }
 __device__ __forceinline__ double r_log_unit(double u) { return log(u); }
-__device__ __forceinline__ uint64_t r_to_u64(float x) { return __float2ull_rn(x); }
-__device__ __forceinline__ uint64_t r_to_u64(double x) { return __double2ull_rn(x); }
 template <typename R> __device__ __forceinline__ R r_inf() { return (R)kInf; }
 template <typename R> __device__ __forceinline__ R clamp01(R x) { return fmin(fmax(x, (R)0), (R)1); }
 template <typename R> __device__ __forceinline__ R u01(uint32_t r) { return (R)(r >> 8) * (R)0x1.0p-24; }
@@ -146,8 +146,10 @@ __device__ __forceinline__ double r_div(double a, double b) { return a / b; }
 // 1/sqrt(x): the hardware reciprocal square root in FP32 (within 1 ulp)
 __device__ __forceinline__ float r_rsqrt(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double r_rsqrt(double x) { return 1.0 / sqrt(x); }
-// 1/|u| per axis, +inf on an axis the photon does not move along
-template <typename R> __device__ __forceinline__ R inv_abs(R u) { return u != (R)0 ? r_rcp(fabs(u)) : r_inf<R>(); }
+// 1/|u| per axis, +inf (1/0) on an axis the photon does not move along.  The distance
+// to that axis's face is then +inf, or NaN (0 x inf) with the photon on it, which a
+// minimum over the axes (fmin) passes over.
+template <typename R> __device__ __forceinline__ R inv_abs(R u) { return r_rcp(fabs(u)); }
 
 // The face distances divide by |u| every step; the quotients are computed once per
 // direction (at launch, deflection and refraction) and kept in the photon state.
@@ -159,6 +161,9 @@ template <typename R> __device__ __forceinline__ void set_direction(Photon<R> &p
     p.iux = inv_abs(ux);
     p.iuy = inv_abs(uy);
     p.iuz = inv_abs(uz);
+    p.bx = ux > (R)0 ? (R)1 : (R)0;
+    p.by = uy > (R)0 ? (R)1 : (R)0;
+    p.bz = uz > (R)0 ? (R)1 : (R)0;
 }
 
 __device__ __forceinline__ uint32_t brick_of(const Job &J, int32_t ix, int32_t iy, int32_t iz)
@@ -391,7 +396,7 @@ __device__ __forceinline__ double free_path(const Job &J, uint32_t r)
 // from 24-bit uniforms scaled by the face size in integer arithmetic, normal
 // incidence (or Lambertian for the test source), first free path.
 template <bool GENERAL, typename R>
-__device__ __forceinline__ void launch(Photon<R> &p, const Job &J, uint32_t pid)
+__device__ __forceinline__ void launch_state(Photon<R> &p, const Job &J, uint32_t pid)
 {
     const U4 r = philox4x32_10(U4{0u, pid, J.stream_id, 0u}, J.key0, J.key1);
     const uint64_t X = (uint64_t)(r.x >> 8) * (uint64_t)J.nx;
@@ -426,6 +431,12 @@ __device__ __forceinline__ void launch(Photon<R> &p, const Job &J, uint32_t pid)
     p.brick = 0xFFFFFFFFu;
     p.l_opt = 0.0;
     p.nf = 0u;
+}
+
+template <bool GENERAL, typename R>
+__device__ __forceinline__ void launch(Photon<R> &p, const Job &J, uint32_t pid)
+{
+    launch_state<GENERAL>(p, J, pid);
     lookup<GENERAL>(p, J);
 }
 
@@ -435,9 +446,10 @@ __device__ __forceinline__ void launch(Photon<R> &p, const Job &J, uint32_t pid)
 // with den = 1 - g + 2 g xi and t = (1 - g^2)/den.  The transverse norm of the
 // old direction is sqrt(ux^2 + uy^2) (= sqrt(1 - uz^2) for a unit vector).
 // Returns cos(theta) (the gradient walk scores it).
-template <typename R>
-__device__ __forceinline__ R scatter(Photon<R> &p, const Job &J, uint32_t r0, uint32_t r1)
+template <class P>
+__device__ __forceinline__ typename P::Real scatter(P &p, const Job &J, uint32_t r0, uint32_t r1)
 {
+    using R = typename P::Real;
     const R g = (R)J.g, xi = u01<R>(r0);
     R ct, st2;
     if (g != (R)0) {
@@ -506,9 +518,10 @@ __device__ __forceinline__ R fresnel(R n1, R n2, R ci, R *ct)
 // its tag-4 Philox stream, a block drawn once per four decisions.  The unused
 // words wait in p.fr and move down one place per draw (a variable word index
 // would force the photon state out of registers).
-template <typename R>
-__device__ __forceinline__ R fresnel_uniform(Photon<R> &p, const Job &J)
+template <class P>
+__device__ __forceinline__ typename P::Real fresnel_uniform(P &p, const Job &J)
 {
+    using R = typename P::Real;
     const uint32_t j = p.nf++;
     if ((j & 3u) == 0u) p.fr = philox4x32_10(U4{j >> 2, p.pid, J.stream_id, 4u}, J.key0, J.key1);
     const uint32_t w = p.fr.x;
@@ -534,14 +547,13 @@ constexpr int32_t EV_AT_INTERACTION = 13;
 template <bool GENERAL, typename R, class Sink>
 __device__ __forceinline__ int32_t advance(Photon<R> &p, const Job &J, Sink &sink)
 {
-    const R dx = p.ux != (R)0 ? (p.ux > (R)0 ? (R)1 - p.fx : p.fx) * p.iux : r_inf<R>();
-    const R dy = p.uy != (R)0 ? (p.uy > (R)0 ? (R)1 - p.fy : p.fy) * p.iuy : r_inf<R>();
-    const R dz = p.uz != (R)0 ? (p.uz > (R)0 ? (R)1 - p.fz : p.fz) * p.iuz : r_inf<R>();
-    int32_t axis = 0;
-    R d_face = dx;
-    R ua = p.ux;              // direction component normal to the face reached
-    if (dy < d_face) { axis = 1; d_face = dy; ua = p.uy; }
-    if (dz < d_face) { axis = 2; d_face = dz; ua = p.uz; }
+    const R dx = fabs(p.bx - p.fx) * p.iux, dy = fabs(p.by - p.fy) * p.iuy, dz = fabs(p.bz - p.fz) * p.iuz;
+    const R d_face = fmin(fmin(dx, dy), dz);
+    const bool on_x = dx == d_face, on_y = !on_x && dy == d_face;
+    const int32_t axis = on_x ? 0 : (on_y ? 1 : 2);
+    R ua = p.uz;              // direction component normal to the face reached
+    if (on_y) ua = p.uy;
+    if (on_x) ua = p.ux;
     const bool solid = p.solid != 0u;
     bool interact = solid && (p.s_rem <= (double)d_face);
     R d = interact ? (R)p.s_rem : d_face;
@@ -560,10 +572,13 @@ __device__ __forceinline__ int32_t advance(Photon<R> &p, const Job &J, Sink &sin
 
     sink.segment(p, J, d, solid);
     if (in_slab) {
-        // track-length deposit, rounded to whole quanta per segment, accumulated while in this voxel
-        p.acc += r_to_u64((R)p.w * d * (R)(1.0 / (1 << kDepositShift)));
-        if (solid) p.s_rem = fmax(p.s_rem - (double)d, 0.0);
-        else p.l_void += (double)d;
+        // track-length deposit, rounded to whole quanta per segment, accumulated while in this voxel;
+        // a segment inside one voxel is shorter than 2 voxel lengths, so its quanta fit 25 bits
+        p.acc += (uint32_t)rint((R)p.w * d * (R)(1.0 / (1 << kDepositShift)));
+        // s_rem -= d in the solid (at an interaction it is drawn anew), l_void += d in a pore: the
+        // products are exact, so each is one addition rounded once
+        p.s_rem = fma((double)d, solid ? -1.0 : 0.0, p.s_rem);
+        p.l_void = fma((double)d, solid ? 0.0 : 1.0, p.l_void);
         p.l_tot += (double)d;
     }
     if constexpr (GENERAL) p.l_opt += n_here * (double)d;
@@ -651,6 +666,9 @@ __device__ __forceinline__ int32_t advance(Photon<R> &p, const Job &J, Sink &sin
             p.ux = axis == 0 ? -p.ux : p.ux;
             p.uy = axis == 1 ? -p.uy : p.uy;
             p.uz = axis == 2 ? -p.uz : p.uz;
+            p.bx = axis == 0 ? (R)1 - p.bx : p.bx;
+            p.by = axis == 1 ? (R)1 - p.by : p.by;
+            p.bz = axis == 2 ? (R)1 - p.bz : p.bz;
             p.fx = axis == 0 ? face : p.fx;
             p.fy = axis == 1 ? face : p.fy;
             p.fz = axis == 2 ? face : p.fz;

@@ -96,6 +96,7 @@ _SIGS = {
     "mc_strerror": (ctypes.c_char_p, [ctypes.c_int]),
     "mc_tune_default": (None, [_P]),
     "mc_run_workspace_bytes": (ctypes.c_size_t, [_P]),
+    "mc_run_extra_workspace_bytes": (ctypes.c_size_t, [_P, ctypes.c_uint64]),
     "mc_run": (ctypes.c_int, [_P, _P, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32,
                               ctypes.c_int, _P, _P, _P, ctypes.c_size_t, _P, _P]),
     "mc_run_escape_histogram": (ctypes.c_int, [_P, _P, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint64,
@@ -315,6 +316,17 @@ def volume(mask: torch.Tensor) -> McVolume:
     return McVolume(nx, ny, nz, 0, mask.data_ptr())
 
 
+def _run_workspace(need: int, vol: McVolume, n_photons: int, device) -> torch.Tensor:
+    """What a run needs, and what a large one makes use of beyond that while the device has it."""
+    extra = load().mc_run_extra_workspace_bytes(ctypes.byref(vol), n_photons) if 0 < n_photons <= 1 << 32 else 0
+    if extra:
+        try:
+            return workspace(need + extra, device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return workspace(need, device)
+
+
 def workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
@@ -344,8 +356,8 @@ def run(mask: torch.Tensor, optics: Optics, n_photons: int, seed: int, photon_be
         flags |= MC_DIRECT_DEPOSIT
     if line_staging:
         flags |= MC_LINE_STAGING
-    nbytes = L.mc_run_workspace_bytes(ctypes.byref(vol))
-    ws = workspace(nbytes, dev)
+    need = L.mc_run_workspace_bytes(ctypes.byref(vol))
+    ws = workspace(need, dev) if direct or line_staging else _run_workspace(need, vol, n_photons, dev)
     opt = optics.c()
     t = tune.c() if tune is not None else None
     tref = ctypes.byref(t) if t is not None else None
@@ -646,7 +658,8 @@ def grad(mask: torch.Tensor, optics: Optics, n_photons: int, seed: int, photon_b
     jac = torch.empty((3, 2 + nz), dtype=torch.float64, device=dev)
     summary = torch.empty(NSUMMARY, dtype=torch.float64, device=dev)
     depth = torch.empty((3, nz), dtype=torch.float64, device=dev)
-    ws = workspace(L.mc_grad_workspace_bytes(ctypes.byref(vol)), dev)
+    need = L.mc_grad_workspace_bytes(ctypes.byref(vol))
+    ws = workspace(need, dev) if line_staging else _run_workspace(need, vol, n_photons, dev)
     opt = optics.c()
     t = tune.c() if tune is not None else None
     flags = (MC_FP64 if fp64 else 0) | (MC_TIMED if timed else 0) | (MC_LINE_STAGING if line_staging else 0)
