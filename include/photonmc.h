@@ -401,6 +401,10 @@ typedef struct {
 /* Workspace (device bytes) a batch of these jobs needs; 0 for an invalid batch. */
 size_t mc_batch_workspace_bytes(const mc_job *jobs, int32_t n_jobs);
 
+/* Further workspace that makes a large batch faster, as mc_run_extra_workspace_bytes does a run; 0 where it
+ * would not be used. */
+size_t mc_batch_extra_workspace_bytes(const mc_job *jobs, int32_t n_jobs);
+
 /*
  * Run 1..MC_MAX_BATCH_JOBS jobs: zero (unless accumulate) and pack every job,
  * one persistent walk over all photons of all jobs (queued longest job first),

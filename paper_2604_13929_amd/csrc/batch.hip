@@ -23,6 +23,7 @@
 #include <string>
 #include <vector>
 
+#include "cells.hpp"
 #include "internal.hpp"
 #include "stage.hpp"
 
@@ -300,6 +301,8 @@ struct Prepared {
     uint64_t total_photons = 0;
     bool general = false;         // some job uses the paper boundary model
     bool planes[MC_MAX_BATCH_JOBS] = {};   // caller's job index -> staged in the plane layout
+    char *cells = nullptr;        // what the workspace has beyond what the batch needs: the cell walk's scratch
+    size_t cells_bytes = 0;
 };
 
 // MC_LINE_STAGING or MC_FP64 in flags keeps every job's staging tally in the line layout.
@@ -318,6 +321,8 @@ int prepare(const mc_job *jobs, int32_t n, char *ws, size_t ws_bytes, int flags,
     }
     P->L = layout_of(jobs, n);
     if (ws_bytes < P->L.total) return fail(MC_ENOSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, P->L.total);
+    P->cells = ws + P->L.total;
+    P->cells_bytes = ws_bytes - P->L.total;
     P->order.resize(n);
     for (int32_t i = 0; i < n; ++i) P->order[i] = i;
     // longest first; ties keep the caller's order
@@ -481,7 +486,13 @@ int enqueue_batch(const mc_job *jobs, const Prepared &P, char *ws, const mc_tune
     }
     const bool timed = (flags & MC_TIMED) != 0;
     if (timed && (rc = time_begin(s))) return rc;
-    if ((rc = enqueue_walk_only(P, ws, t, flags, s, bins != nullptr))) return rc;
+    const CellRun cells = {P.table.data(), n, P.total_photons, P.general, (flags & MC_FP64) != 0, nullptr,
+                           bins ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr, nullptr, P.cells, P.cells_bytes};
+    if (!(flags & MC_LINE_STAGING) && cell_walk_fits(cells)) {
+        if ((rc = cell_walk(cells, s))) return rc;
+    } else if ((rc = enqueue_walk_only(P, ws, t, flags, s, bins != nullptr))) {
+        return rc;
+    }
     if (timed && (rc = time_end(s))) return rc;
     if (bins) {
         if ((rc = fold_esc((const BatchEsc *)(ws + P.L.esc_off), n, s))) return rc;
@@ -732,6 +743,19 @@ size_t mc_batch_workspace_bytes(const mc_job *jobs, int32_t n_jobs)
     for (int32_t i = 0; i < n_jobs; ++i)
         if (check_volume(&jobs[i].vol)) return 0;
     return layout_of(jobs, n_jobs).total;
+}
+
+size_t mc_batch_extra_workspace_bytes(const mc_job *jobs, int32_t n_jobs)
+{
+    if (!jobs || n_jobs < 1 || n_jobs > MC_MAX_BATCH_JOBS) return 0;
+    CellDims d[MC_MAX_BATCH_JOBS];
+    uint64_t photons = 0;
+    for (int32_t i = 0; i < n_jobs; ++i) {
+        if (check_volume(&jobs[i].vol) || jobs[i].n_photons > (1ull << 32)) return 0;
+        d[i] = cell_dims(&jobs[i].vol, jobs[i].opt.boundary == MC_BOUNDARY_PAPER);
+        photons += jobs[i].n_photons;
+    }
+    return cell_workspace_bytes(d, n_jobs, photons);
 }
 
 int mc_autotune_batch(const mc_job *jobs, int32_t n_jobs, int flags, void *workspace, size_t workspace_bytes,

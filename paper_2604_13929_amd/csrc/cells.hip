@@ -48,11 +48,15 @@ constexpr int kSortBlocks = 256;
 constexpr int kSortThreads = 1024;
 constexpr int32_t kMaxCells = 32768;
 constexpr uint32_t kMinItem = 2048, kMaxItem = 65536;   // photons of an item
-// Photons alive at which the rounds end.  A round has a fixed cost (launches, and a cell's mask in and
-// tally out for each cell), the tail runs at the deposit log's rate: the sum was lowest, for 256^3
-// (512 cells), at 0.7e6 to 1e6 alive (1e7 photons: 74 ms; 77 at 0.5e6, 83 at 2e6), for 96 x 112 x 128
-// (48 cells) flat from 0.5e6 to 1e6, for 512 x 512 x 256 (2048 cells) at 2e6 (112 ms; 150 at 0.7e6).
-constexpr uint32_t kStopPerCu = 2560, kStopPerCell = 640;
+// When the rounds end: a round has a fixed cost (launches, and a cell's mask in and tally out for each cell
+// taken), the tail runs at the deposit log's rate.  Ending at less than kStopPerCu photons per compute unit and
+// kStopPerCell per cell measured lowest or within 2 % of it for 256^3 (512 cells, 1e7 photons: 75 ms; 80 at
+// 0.33e6 photons whatever the cells), 512 x 512 x 256 (2048 cells, 2e7 photons: 118 ms; 147) and a batch of 12
+// volumes (69 ms; 104).  A cell with fewer than kLeastPerCell photons is not taken: they wait for more to
+// come (the batch: 77 ms with every cell taken, 75 from 256 photons on, 70 from 512, 69 from 1024; 256^3 loses
+// 6 % at 4096).
+constexpr uint32_t kStopPerCu = 2560;
+constexpr uint32_t kStopPerCell = 640, kLeastPerCell = 1024;
 // The least photons of a run in rounds: the deposit log alone is as fast at 2e6 (100 x 90 x 110 voxels, 3e6
 // photons: 19.1 against 21.8 ms; 1e6: 12.6 against 10.1).
 constexpr uint64_t kMinPhotons = 2000000;
@@ -68,7 +72,7 @@ struct Ctrl {
     unsigned long long total;              // queue positions
     uint32_t n_items, item_cursor;
     uint32_t alive, done, arrived;
-    uint32_t stop_at;                      // rounds end once no more than this many photons are alive
+    uint32_t stop_at;                      // rounds end once no more photons than this (and kStopPerCell a cell) are worth one
     unsigned long long tail_next;
     uint32_t n_jobs, n_cells, slots, walkers;   // walkers: workgroups of the walk
 };
@@ -444,7 +448,7 @@ __device__ __forceinline__ uint32_t item_class(uint32_t n, uint32_t W) { return 
 __global__ __launch_bounds__(kSortThreads) void k_cells_scatter(Tables T, int32_t force)
 {
     extern __shared__ uint32_t s_hist[];
-    __shared__ uint32_t s_part[kSortThreads / 64], s_alive, s_class[kClasses];
+    __shared__ uint32_t s_part[kSortThreads / 64], s_alive, s_class[kClasses], s_used, s_cells;
     Ctrl *c = T.ctrl;
     if (c->done == 2u) return;
     const uint32_t cells = c->n_cells, slots = c->slots;
@@ -468,12 +472,24 @@ __global__ __launch_bounds__(kSortThreads) void k_cells_scatter(Tables T, int32_
         const uint32_t W = min(max(alive / c->walkers, kMinItem), kMaxItem);
         // the items by size, largest first: each workgroup of the walk takes the next one when it is
         // done with its last, and the short ones even out the end
+        // a cell with few photons lets them wait until there are more: taking it costs a workgroup as much
+        // time as some 1000 visits.  At least half of the photons are in cells that are taken.
+        const uint32_t least = min(kLeastPerCell, alive / (2u * cells));
+        uint32_t mine_used = 0u, mine_cells = 0u;
         if (threadIdx.x < kClasses) s_class[threadIdx.x] = 0u;
+        if (threadIdx.x == 0) s_used = s_cells = 0u;
         __syncthreads();
         for (uint32_t i = c0; i < c1; ++i) {
             const uint32_t k = T.count[i];
+            if (k < least) continue;
+            mine_used += k;
+            ++mine_cells;
             if (k >= W) atomicAdd(&s_class[0], k / W);
             if (k % W) atomicAdd(&s_class[item_class(k % W, W)], 1u);
+        }
+        if (mine_cells) {
+            atomicAdd(&s_used, mine_used);
+            atomicAdd(&s_cells, mine_cells);
         }
         __syncthreads();
         uint32_t n_items = 0u;
@@ -486,7 +502,12 @@ __global__ __launch_bounds__(kSortThreads) void k_cells_scatter(Tables T, int32_
         __syncthreads();
         off = first;
         for (uint32_t i = c0; i < c1; ++i) {
-            for (uint32_t k = T.count[i]; k != 0u;) {
+            uint32_t k = T.count[i];
+            if (k < least) {
+                off += k;
+                continue;
+            }
+            while (k != 0u) {
                 const uint32_t n = min(k, W);
                 T.items[atomicAdd(&s_class[item_class(n, W)], 1u)] = Item{i, off, off + n, 0u};
                 off += n;
@@ -494,7 +515,7 @@ __global__ __launch_bounds__(kSortThreads) void k_cells_scatter(Tables T, int32_
             }
         }
         if (threadIdx.x == 0) {
-            const bool stop = force || (c->next_id >= c->total && alive <= c->stop_at);
+            const bool stop = force || (c->next_id >= c->total && s_used <= c->stop_at + kStopPerCell * s_cells);
             c->alive = alive;
             c->n_items = stop ? 0u : n_items;
             c->item_cursor = 0u;
@@ -1256,8 +1277,6 @@ size_t cell_workspace_bytes(const CellDims *dims, int32_t n_jobs, uint64_t photo
     return up256(lay_tables(nullptr, cells, n_jobs, &P) + kSlack + std::min(photons + 4, wanted_slots(cells)) * (4 * 16 + 8));
 }
 
-static uint32_t stop_count(uint64_t cells, int cus) { return (uint32_t)cus * kStopPerCu + (uint32_t)cells * kStopPerCell; }
-
 bool cell_walk_fits(const CellRun &r)
 {
     DeviceInfo di;
@@ -1269,7 +1288,7 @@ bool cell_walk_fits(const CellRun &r)
     }
     Plan P;
     if (!plan_of(r, &P)) return false;
-    const uint64_t least = std::max<uint64_t>(kMinPhotons, 2ull * stop_count(P.cells, di.cus));
+    const uint64_t least = std::max<uint64_t>(kMinPhotons, 2ull * di.cus * kStopPerCu);
     return r.photons >= least && P.slots >= least / 2;
 }
 
@@ -1295,7 +1314,7 @@ int cell_walk(const CellRun &r, hipStream_t s)
         hipLaunchKernelGGL(k_cells_jobs, dim3(1), dim3(256), 0, s, pack, (Job *)P.T.jobs + i, (Grid *)P.T.grids + i, c);
         HIP_TRY(hipGetLastError());
     }
-    const uint32_t stop_at = stop_count(P.cells, di.cus);
+    const uint32_t stop_at = (uint32_t)di.cus * kStopPerCu;
     hipLaunchKernelGGL(k_cells_setup, dim3(1024), dim3(256), 0, s, P.T, r.photons, (uint32_t)r.n_jobs, (uint32_t)P.cells,
                        P.slots, stop_at, (uint32_t)di.cus);
     HIP_TRY(hipGetLastError());
@@ -1310,13 +1329,15 @@ int cell_walk(const CellRun &r, hipStream_t s)
     }
     // a photon's visits: a path of three slab thicknesses over the mean chord 4V/S of a cell (256^3 workload: 36,
     // 32 observed); the photons alive fall by a factor e in 1.4 times as many rounds
-    double visits = 0.0;
+    double longest = 0.0, launches = 0.0;
     for (int32_t i = 0; i < r.n_jobs; ++i) {
         const CellDims &d = P.d[i];
-        visits = std::max(visits, 3.0 * r.table[i].nz * 0.5 * (1.0 / d.ex + 1.0 / d.ey + 1.0 / d.ez));
+        const double visits = 3.0 * r.table[i].nz * 0.5 * (1.0 / d.ex + 1.0 / d.ey + 1.0 / d.ez);
+        longest = std::max(longest, visits);
+        launches += visits * (double)r.table[i].n_photons / P.slots;
     }
     const double decay = 1.4 * std::max(0.0, log((double)P.slots / stop_at));
-    const int rounds = (int)std::min(4000.0, 8.0 + visits * ((double)r.photons / P.slots + decay));
+    const int rounds = (int)std::min(4000.0, 8.0 + launches + longest * decay);
     if (r.fp64) rc = enqueue_general<double>(r, P, rounds, di.cus, esc, s);
     else rc = enqueue_general<float>(r, P, rounds, di.cus, esc, s);
     if (rc) return rc;

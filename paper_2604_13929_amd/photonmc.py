@@ -114,6 +114,7 @@ _SIGS = {
     "mc_grad": (ctypes.c_int, [_P, _P, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32,
                                ctypes.c_int, _P, _P, _P, _P, _P, _P, _P, ctypes.c_size_t, _P, _P]),
     "mc_batch_workspace_bytes": (ctypes.c_size_t, [_P, ctypes.c_int32]),
+    "mc_batch_extra_workspace_bytes": (ctypes.c_size_t, [_P, ctypes.c_int32]),
     "mc_run_batch": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.c_int, _P, _P, ctypes.c_size_t, _P]),
     "mc_run_batch_escape_histogram": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.c_int, _P, _P, _P,
                                                      ctypes.c_size_t, _P]),
@@ -317,8 +318,13 @@ def volume(mask: torch.Tensor) -> McVolume:
 
 
 def _run_workspace(need: int, vol: McVolume, n_photons: int, device) -> torch.Tensor:
-    """What a run needs, and what a large one makes use of beyond that while the device has it."""
+    """What a run needs, and what a large one makes use of beyond that."""
     extra = load().mc_run_extra_workspace_bytes(ctypes.byref(vol), n_photons) if 0 < n_photons <= 1 << 32 else 0
+    return _extra_workspace(need, extra, device)
+
+
+def _extra_workspace(need: int, extra: int, device) -> torch.Tensor:
+    """need + extra bytes while the device has them, else what is needed."""
     if extra:
         try:
             return workspace(need + extra, device)
@@ -534,7 +540,7 @@ class Batch:
         nbytes = L.mc_batch_workspace_bytes(ctypes.byref(arr), len(jobs))
         if nbytes == 0:
             raise McError(-1, "mc_batch_workspace_bytes", "invalid batch")
-        self.ws = workspace(nbytes, dev)
+        self.ws = _extra_workspace(nbytes, L.mc_batch_extra_workspace_bytes(ctypes.byref(arr), len(jobs)), dev)
 
     def attach_escape_bins(self, escape_bins: list, accumulate_into: "Batch | None" = None):
         """Per-job escape-path histograms: escape_bins[i] = (bin_width, nbins) or None.

@@ -124,3 +124,45 @@ def test_few_photons_spread_over_wavefronts(n):
     a = pm.run(mask, PLAIN, n, SEED)
     b = pm.run(mask, PLAIN, n, SEED, direct=True, tune=pm.Tune(block=64, waves_per_cu=3, chunk=7, refill=64, defer=64))
     _same((a.fluence, a.scalars), (b.fluence, b.scalars))
+
+
+def _jobs(paper):
+    rng = np.random.default_rng(8)
+    jobs = []
+    for i, dims in enumerate([(33, 20, 40), (64, 64, 30), (5, 6, 31), (40, 40, 40), (20, 70, 33)]):
+        opt = pm.Optics(0.2 + 0.1 * i, 0.01, 0.1 * i)
+        if paper and i % 2:
+            opt = pm.paper_optics(0.3, 0.01, 0.5, gate=500.0, lateral=i // 2)
+        jobs.append(pm.BatchJob(_mask(*dims), opt, int(rng.integers(300_000, 700_000)), SEED, stream_id=i,
+                                photon_begin=11 * i, reduce=i != 2))
+    return jobs
+
+
+@pytest.mark.parametrize("paper,fp64,esc", [(False, False, False), (False, False, True), (True, False, True),
+                                            (True, True, False)])
+def test_batch_cells_equal_log(paper, fp64, esc):
+    """Jobs of several cells each, some narrower than one, in one batch of more than 2e6 photons."""
+    jobs = _jobs(paper)
+    assert sum(j.n_photons for j in jobs) >= 2_000_000
+    bins = [(4.0, 50 + i) if i != 1 else None for i in range(len(jobs))] if esc else None
+    a = pm.run_batch(jobs, tune=pm.Tune(), fp64=fp64, escape_bins=bins)
+    b = pm.run_batch(jobs, tune=pm.Tune(), fp64=fp64, escape_bins=bins, line_staging=True)
+    for x, y in zip(a.results, b.results):
+        _same((x.fluence, x.scalars), (y.fluence, y.scalars))
+        if x.escape_hist_w is not None:
+            _same((x.escape_hist_w, x.escape_hist_n), (y.escape_hist_w, y.escape_hist_n))
+
+
+def test_batch_graph_in_cells():
+    """The captured step of a large batch, replayed with eager work in between."""
+    jobs = _jobs(False)
+    want = pm.run_batch(jobs, tune=pm.Tune(), line_staging=True)
+    graph = pm.BatchGraph(jobs, tune=pm.Tune())
+    for _ in range(3):
+        for r in graph.batch.results:
+            r.fluence.fill_(7)
+        graph.launch()
+        torch.cuda.synchronize()
+        for x, y in zip(graph.batch.results, want.results):
+            _same((x.fluence, x.scalars), (y.fluence, y.scalars))
+    graph.close()
