@@ -4,7 +4,7 @@
 // binarisation.
 //
 // Design (gfx950): the spectrum lives in HBM as complex double [nz][ny][nx/2+1].
-// Every transform is a Stockham FFT (radices 2, 3, 4) over whole lines held in
+// Every transform is a Stockham FFT (radices 2 to 16) over whole lines held in
 // LDS, 4096 complex values per 256-thread workgroup, so one line is read and
 // written once per pass.  One time step is four in-place passes over the
 // spectrum-sized work array W, with the state S touched only in the z pass:
@@ -41,30 +41,34 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kLdsElems = 4096;           // complex doubles transformed per workgroup (64 KiB)
 constexpr int kColRadixLog = 2;           // k_colpass keeps radix-4 stages (measured faster there)
-constexpr int kColElems = kLdsElems + 64; // LDS of the column passes: lines padded to n + 1
 constexpr int kMaxStages = 12;
 constexpr int kMaxN = 1024;
 constexpr int kTwElems = 768;             // LDS twiddles: n/2 for even n (w(m + n/2) = -w(m)), n for odd n <= 729
 constexpr int kPadElems = 4400;           // LDS of the compile-time lengths: lines padded by one per 16
+constexpr int kColElems = 4336;           // LDS of the other lengths, whose twiddles take more: two workgroups per CU
 constexpr int kPadTw = 528;               // their twiddles: n/2 padded by one per 32
 // The x pass of the compile-time lengths takes 2048 complex values per workgroup
 // (two or more line pairs): 35 KB of LDS with the padding, 43 KB with the
 // twiddles, so three workgroups share a CU (at 1024: 2003 us against 2200 with
 // 4096 values, two workgroups per CU, and 2185 with 1024 values, one pair).
+constexpr int kFewGroups = 512;           // workgroups a pass should have at least
 constexpr int kXElems = 2048;
 constexpr int kXPadElems = 2200;
 
 // LDS index of element i of a line: the compile-time lengths insert one pad
 // element per 16 (and one per 32 in the twiddle table), which spreads the
 // strided accesses of the early and middle stages over the banks.
-template <int N> __device__ __forceinline__ int pidx(int i) { return N > 0 ? i + (i >> 4) : i; }
+template <int N> __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
 template <int N> __device__ __forceinline__ int tidx(int i) { return N > 0 ? i + (i >> 5) : i; }
 
 // Host-side geometry of the LDS layouts (must match the kernels).
-constexpr bool static_length(int n) { return n == 1024 || n == 512 || n == 384 || n == 256; }
+constexpr bool static_length(int n)
+{
+    return n == 1024 || n == 768 || n == 512 || n == 384 || n == 256 || n == 192 || n == 128 || n == 96 || n == 64;
+}
 inline int line_stride(int n, bool column)
 {
-    return static_length(n) ? n + n / 16 + (column ? 1 : 0) : n + (column ? 1 : 0);
+    return n + n / 16 + (column ? 1 : 0);
 }
 
 // Per-stage constants, with FP32 reciprocals for the index divisions.
@@ -88,7 +92,9 @@ __device__ __forceinline__ int fdiv(int x, int d, float inv)
     return q;
 }
 
-// radix-3 stages first, then radix 4, then one radix 2 if the power of two is odd
+// The stages of a length without a compile-time plan: radix 9 (and one 3), then the power of two 2^t in
+// ceil(t / 4) stages of radix 16, 8, 4 or 2 as even as possible: the fewest passes through LDS (a step of
+// 324 x 729 x 192: 1160 us; 1373 with radices 2, 3 and 4; 288^3: 584 against 725).
 bool make_plan(int n, Plan *p)
 {
     memset(p, 0, sizeof *p);
@@ -98,9 +104,10 @@ bool make_plan(int n, Plan *p)
     while (m % 2 == 0) { m /= 2; ++twos; }
     if (m != 1) return false;
     int s = 0;
-    for (int i = 0; i < threes; ++i) p->radix[s++] = 3;
-    for (int i = 0; i < twos / 2; ++i) p->radix[s++] = 4;
-    if (twos % 2) p->radix[s++] = 2;
+    for (int i = 0; i < threes / 2; ++i) p->radix[s++] = 9;
+    if (threes % 2) p->radix[s++] = 3;
+    const int two_stages = (twos + 3) / 4;
+    for (int i = 0; i < two_stages; ++i) p->radix[s++] = 1 << (twos / two_stages + (i < twos % two_stages ? 1 : 0));
     p->nstages = s;
     int ns = 1;
     for (int i = 0; i < s; ++i) {
@@ -206,6 +213,35 @@ template <> __device__ __forceinline__ void dft<3>(double2 *v, bool inv)
     }
 }
 
+// radix 9 as 3 x 3: radix-3 DFTs over n1 of v[3 n1 + n2], twiddles w9^(n2 k1), radix-3 DFTs over n2
+// giving X[k1 + 3 k2]
+template <> __device__ __forceinline__ void dft<9>(double2 *v, bool inv)
+{
+    // cos and sin of 2 pi m / 9, m = 1, 2, 4
+    constexpr double c[3] = {0.76604444311897803520, 0.17364817766693034885, -0.93969262078590838405};
+    constexpr double sn[3] = {0.64278760968653932632, 0.98480775301220805937, 0.34202014332566873304};
+    const double sg = inv ? 1.0 : -1.0;
+    double2 a[3][3];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+        double2 t[3] = {v[n2], v[3 + n2], v[6 + n2]};
+        dft<3>(t, inv);
+#pragma unroll
+        for (int k1 = 0; k1 < 3; ++k1) {
+            const int m = n2 * k1;                       // 0, 1, 2 or 4
+            const int i = m == 4 ? 2 : m - 1;
+            a[n2][k1] = m == 0 ? t[k1] : cmul(t[k1], make_double2(c[i < 0 ? 0 : i], sg * sn[i < 0 ? 0 : i]));
+        }
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+        double2 t[3] = {a[0][k1], a[1][k1], a[2][k1]};
+        dft<3>(t, inv);
+#pragma unroll
+        for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = t[k2];
+    }
+}
+
 // One Stockham stage of radix R over `nlines` lines of length n in LDS (line l
 // at buf + l * ls): butterfly j of a line reads elements j + r n/R, twiddles
 // them by w^(r (j mod ns)) with w = exp(-+ 2 pi i / (ns R)), transforms, and
@@ -220,18 +256,19 @@ __device__ __forceinline__ void stage(double2 *buf, int n, int ns, int nlines, i
     const int total = nlines * nb;
     const int tstep = n / (ns * R);
     double2 v[kPer][R];
-    int dst[kPer];
+    int dst[kPer], dst2[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int b = (int)threadIdx.x + q * kThreads;
         dst[q] = -1;
+        dst2[q] = 0;
         if (b < total) {
             const int line = fdiv(b, nb, inv_nb), j = b - line * nb;
             const int jm = j - fdiv(j, ns, inv_ns) * ns;
             const double2 *src = buf + line * ls;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                double2 x = src[j + r * nb];
+                double2 x = src[pidx<0>(j + r * nb)];
                 if (r) {
                     int m = jm * r * tstep;
                     double sg = 1.0;
@@ -247,7 +284,8 @@ __device__ __forceinline__ void stage(double2 *buf, int n, int ns, int nlines, i
                 v[q][r] = x;
             }
             dft<R>(v[q], inv);
-            dst[q] = line * ls + (j - jm) * R + jm;
+            dst[q] = line * ls;
+            dst2[q] = (j - jm) * R + jm;
         }
     }
     __syncthreads();
@@ -255,7 +293,7 @@ __device__ __forceinline__ void stage(double2 *buf, int n, int ns, int nlines, i
     for (int q = 0; q < kPer; ++q) {
         if (dst[q] >= 0) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) buf[dst[q] + r * ns] = v[q][r];
+            for (int r = 0; r < R; ++r) buf[dst[q] + pidx<0>(dst2[q] + r * ns)] = v[q][r];
         }
     }
     __syncthreads();
@@ -276,7 +314,10 @@ __device__ void fft_lines(double2 *buf, int ls, int nlines, const Plan &P, const
 {
     for (int s = 0; s < P.nstages; ++s) {
         const int R = P.radix[s], ns = P.ns[s];
-        if (R == 4) stage<4>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
+        if (R == 16) stage<16>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
+        else if (R == 9) stage<9>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
+        else if (R == 8) stage<8>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
+        else if (R == 4) stage<4>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
         else if (R == 2) stage<2>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
         else stage<3>(buf, P.n, ns, nlines, ls, inv, tw, P.inv_nb[s], P.inv_ns[s]);
     }
@@ -439,11 +480,11 @@ __global__ __launch_bounds__(kThreads) void k_xpass(const double *__restrict__ r
                                                      Plan P, const double2 *__restrict__ tw, double scale,
                                                      const uint8_t *__restrict__ mask_in)
 {
-    __shared__ double2 buf[N > 0 ? kXPadElems : kLdsElems];
+    __shared__ double2 buf[kXPadElems];
     __shared__ double2 tw_s[N > 0 ? kPadTw : kTwElems];
     load_twiddles<N>(tw_s, tw, nx);
     double *bd = reinterpret_cast<double *>(buf);   // bd[2 p] = buf[p].x, bd[2 p + 1] = buf[p].y
-    const int hx = nx / 2 + 1, half = nx / 2, ls = N > 0 ? nx + nx / 16 : nx;
+    const int hx = nx / 2 + 1, half = nx / 2, ls = nx + nx / 16;
     const int line0 = (int)blockIdx.x * L;
     const int nl = min(L, nlines_total - line0);
     const int np = (nl + 1) >> 1;
@@ -547,7 +588,7 @@ __global__ __launch_bounds__(kThreads) void k_colpass(double2 *A, int ny, int hx
     const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int p = bid / tiles, tile = bid - p * tiles;
     // lines padded to an odd stride: the transposing loads hit distinct banks
-    const int x0 = tile * T, nc = min(T, hx - x0), ls = (N > 0 ? n + n / 16 : n) + 1;
+    const int x0 = tile * T, nc = min(T, hx - x0), ls = n + n / 16 + 1;
     const int tid = (int)threadIdx.x;
     const float inv_nc = 1.0f / (float)nc;
     gather<8, double2>(
@@ -586,7 +627,7 @@ __global__ __launch_bounds__(kThreads) void k_zpass(double2 *S, double2 *W, int 
     load_twiddles<N>(tw_s, tw, nz);
     const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int y = bid / tiles, tile = bid - y * tiles;
-    const int x0 = tile * T, nc = min(T, hx - x0), ls = (N > 0 ? nz + nz / 16 : nz) + 1;
+    const int x0 = tile * T, nc = min(T, hx - x0), ls = nz + nz / 16 + 1;
     const int tid = (int)threadIdx.x;
     const float inv_nc = 1.0f / (float)nc;
     const double2 *src = MODE == Z_INV ? S : W;
@@ -717,18 +758,19 @@ int geometry(const mc_ch_grid *g, Geo *G)
     if (!make_plan(g->nx, &G->px) || !make_plan(g->ny, &G->py) || !make_plan(g->nz, &G->pz))
         return fail(MC_EINVAL, "every extent must be a product of powers of 2 and 3");
     G->spec_elems = (size_t)G->nz * G->ny * G->hx;
-    // two real lines per complex transform
-    G->Lx = 2 * std::max(1, (static_length(G->nx) ? kXElems : kLdsElems) / G->nx);
-    // column tiles: padded lines must fit the LDS buffer and the stage registers
-    auto tile = [](int n, int lds_static, int elems_static) {
-        const int lds = static_length(n) ? lds_static : kColElems;
-        const int elems = static_length(n) ? elems_static : kLdsElems;
-        return std::max(1, std::min(lds / line_stride(n, true), elems / n));
+    // Two real lines per complex transform, kXElems values of them per workgroup; column tiles whose padded lines
+    // fit the LDS buffer.  (The full tile for z too: half-size z tiles, three workgroups per CU and 80-byte column
+    // runs, measured slower, 3602 against 3468 us at 384 x 1024 x 1024.)  A grid too small to give every CU two
+    // workgroups that way takes smaller shares, down to one pair of lines and runs of 8 columns (128 bytes): a step of
+    // 128 x 64 x 96 (96 to 192 workgroups a pass with full shares) 55 us against 84, 64^3 31 against 59.
+    auto share = [](int count, int most, int least, int others) {
+        const int parts = std::max((count + most - 1) / most, std::min((count + least - 1) / least, (kFewGroups + others - 1) / others));
+        return (count + parts - 1) / parts;
     };
-    G->Ty = tile(G->ny, kPadElems, kLdsElems);
-    // the full tile for z too: half-size z tiles (three workgroups per CU, 80-byte
-    // column runs) measured slower, 3602 against 3468 us at 384 x 1024 x 1024
-    G->Tz = tile(G->nz, kPadElems, kLdsElems);
+    auto most = [](int n) { return std::max(1, std::min((static_length(n) ? kPadElems : kColElems) / line_stride(n, true), kLdsElems / n)); };
+    G->Lx = 2 * share((G->nz * G->ny + 1) / 2, std::max(1, kXElems / G->nx), 1, 1);
+    G->Ty = share(G->hx, most(G->ny), 8, G->nz);
+    G->Tz = share(G->hx, most(G->nz), 8, G->ny);
     G->tiles_y = (G->hx + G->Ty - 1) / G->Ty;
     G->tiles_z = (G->hx + G->Tz - 1) / G->Tz;
     size_t off = 0;
@@ -788,15 +830,22 @@ int prepare(const mc_ch_grid *g, void *ws, size_t ws_bytes, hipStream_t s, Geo *
     return MC_OK;
 }
 
-// Lengths with a compile-time plan; any other length takes the runtime plan.
+// Lengths with a compile-time plan: 2^k and 3 2^k from 64 to 1024.  Any other length takes the runtime plan, which
+// carries every radix and divides at run time (a step of 128 x 64 x 96 takes 44 us with compile-time plans,
+// 55 without; 192^3: 169 against 191).
 template <class F>
 void with_length(int n, F &&f)
 {
     switch (n) {
     case 1024: f(std::integral_constant<int, 1024>{}); break;
+    case 768: f(std::integral_constant<int, 768>{}); break;
     case 512: f(std::integral_constant<int, 512>{}); break;
     case 384: f(std::integral_constant<int, 384>{}); break;
     case 256: f(std::integral_constant<int, 256>{}); break;
+    case 192: f(std::integral_constant<int, 192>{}); break;
+    case 128: f(std::integral_constant<int, 128>{}); break;
+    case 96: f(std::integral_constant<int, 96>{}); break;
+    case 64: f(std::integral_constant<int, 64>{}); break;
     default: f(std::integral_constant<int, 0>{}); break;
     }
 }
