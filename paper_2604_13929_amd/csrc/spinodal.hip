@@ -40,17 +40,14 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kLdsElems = 4096;           // complex doubles transformed per workgroup (64 KiB)
-constexpr int kColRadixLog = 2;           // k_colpass keeps radix-4 stages (measured faster there)
 constexpr int kMaxStages = 12;
 constexpr int kMaxN = 1024;
 constexpr int kTwElems = 768;             // LDS twiddles: n/2 for even n (w(m + n/2) = -w(m)), n for odd n <= 729
 constexpr int kPadElems = 4400;           // LDS of the compile-time lengths: lines padded by one per 16
 constexpr int kColElems = 4336;           // LDS of the other lengths, whose twiddles take more: two workgroups per CU
 constexpr int kPadTw = 528;               // their twiddles: n/2 padded by one per 32
-// The x pass of the compile-time lengths takes 2048 complex values per workgroup
-// (two or more line pairs): 35 KB of LDS with the padding, 43 KB with the
-// twiddles, so three workgroups share a CU (at 1024: 2003 us against 2200 with
-// 4096 values, two workgroups per CU, and 2185 with 1024 values, one pair).
+// The x pass takes 2048 complex values per workgroup (one or more line pairs): 35 KB
+// of LDS with the padding, 43 to 47 KB with the twiddles, so three workgroups share a CU.
 constexpr int kFewGroups = 512;           // workgroups a pass should have at least
 constexpr int kXElems = 2048;
 constexpr int kXPadElems = 2200;
@@ -58,7 +55,7 @@ constexpr int kXPadElems = 2200;
 // LDS index of element i of a line: the compile-time lengths insert one pad
 // element per 16 (and one per 32 in the twiddle table), which spreads the
 // strided accesses of the early and middle stages over the banks.
-template <int N> __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
+__device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
 template <int N> __device__ __forceinline__ int tidx(int i) { return N > 0 ? i + (i >> 5) : i; }
 
 // Host-side geometry of the LDS layouts (must match the kernels).
@@ -268,7 +265,7 @@ __device__ __forceinline__ void stage(double2 *buf, int n, int ns, int nlines, i
             const double2 *src = buf + line * ls;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                double2 x = src[pidx<0>(j + r * nb)];
+                double2 x = src[pidx(j + r * nb)];
                 if (r) {
                     int m = jm * r * tstep;
                     double sg = 1.0;
@@ -293,7 +290,7 @@ __device__ __forceinline__ void stage(double2 *buf, int n, int ns, int nlines, i
     for (int q = 0; q < kPer; ++q) {
         if (dst[q] >= 0) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) buf[dst[q] + pidx<0>(dst2[q] + r * ns)] = v[q][r];
+            for (int r = 0; r < R; ++r) buf[dst[q] + pidx(dst2[q] + r * ns)] = v[q][r];
         }
     }
     __syncthreads();
@@ -329,7 +326,7 @@ __device__ void fft_lines(double2 *buf, int ls, int nlines, const Plan &P, const
 // 384 = 3 16 8, 256 = 16 16): fewer passes through LDS than radix 4.
 constexpr int c_threes(int n) { int t = 0; while (n % 3 == 0) { n /= 3; ++t; } return t; }
 constexpr int c_twos(int n) { while (n % 3 == 0) n /= 3; int t = 0; while (n % 2 == 0) { n /= 2; ++t; } return t; }
-// ML: largest radix 2^ML (4: up to 16; 2: radix 4 only)
+// ML: largest radix 2^ML
 constexpr int c_two_stages(int n, int ML) { return (c_twos(n) + ML - 1) / ML; }
 constexpr int c_stages(int n, int ML) { return c_threes(n) + c_two_stages(n, ML); }
 constexpr int c_radix(int n, int s, int ML)
@@ -346,79 +343,141 @@ constexpr int c_ns(int n, int s, int ML)
     return p;
 }
 
-template <int R, int N, int NS, bool INV>
-__device__ __forceinline__ void stage_c(double2 *buf, int ls, int nlines, const double2 *tw)
+// The plan of length N (REV: its radices in reverse order): radix and product of the radices before stage S.
+template <int N, bool REV, int S> constexpr int p_radix() { return c_radix(N, REV ? c_stages(N, 4) - 1 - S : S, 4); }
+template <int N, bool REV, int S> constexpr int p_ns()
 {
-    constexpr int NB = N / R;
-    constexpr int TSTEP = N / (NS * R);
-    constexpr int kPer = (kLdsElems / R + kThreads - 1) / kThreads;
+    int p = 1;
+    for (int i = 0; i < S; ++i) p *= c_radix(N, REV ? c_stages(N, 4) - 1 - i : i, 4);
+    return p;
+}
+
+// Butterfly b of a stage of NB butterflies per line.  Lines in memory order (COL false): a line's butterflies
+// on consecutive threads.  Columns (COL true): the lines, which are neighbours in memory, on consecutive threads.
+template <bool COL, int NB> __device__ __forceinline__ void butterfly(int b, int nlines, float inv_nlines, int &line, int &j)
+{
+    if (COL) {
+        j = fdiv(b, nlines, inv_nlines);
+        line = b - j * nlines;
+    } else {
+        line = b / NB;
+        j = b - line * NB;
+    }
+}
+
+template <int N, bool INV> __device__ __forceinline__ double2 twiddle(double2 x, int m, const double2 *tw)
+{
+    const bool hi = m >= N / 2;
+    double2 w = tw[tidx<N>(hi ? m - N / 2 : m)];
+    if (hi) w = make_double2(-w.x, -w.y);
+    if (INV) w.y = -w.y;
+    return cmul(x, w);
+}
+
+// One stage of radix R of the lines a workgroup holds (at most ELEMS values): load(line, element) gives a value,
+// store(line, element, value) takes one.  The first stage of a transform loads from memory and the last one may
+// store there, so that a line passes through LDS once between two stages and not once more at each end.
+// `wait`: the values are stored where they were loaded from (LDS), so all are loaded first.
+template <int R, int N, int NS, bool INV, bool COL, int ELEMS, class Load, class Store>
+__device__ __forceinline__ void fft_stage(int nlines, float inv_nlines, const double2 *tw, bool wait, Load load, Store store)
+{
+    constexpr int NB = N / R, TSTEP = N / (NS * R), kPer = (ELEMS / R + kThreads - 1) / kThreads;
     const int total = nlines * NB;
     double2 v[kPer][R];
-    int dst[kPer], dst2[kPer];
+    int line[kPer], j[kPer];
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int b = (int)threadIdx.x + q * kThreads;
-        dst[q] = -1;
-        dst2[q] = 0;
+        line[q] = -1;
         if (b < total) {
-            const int line = b / NB, j = b - line * NB;
-            const int jm = j % NS;
-            const double2 *src = buf + line * ls;
+            butterfly<COL, NB>(b, nlines, inv_nlines, line[q], j[q]);
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                double2 x = src[pidx<N>(j + r * NB)];
-                if (r) {
-                    int m = jm * r * TSTEP;
-                    double2 w;
-                    if constexpr ((N & 1) == 0) {
-                        const bool hi = m >= N / 2;
-                        w = tw[tidx<N>(hi ? m - N / 2 : m)];
-                        if (hi) w = make_double2(-w.x, -w.y);
-                    } else {
-                        w = tw[tidx<N>(m)];
-                    }
-                    if (INV) w.y = -w.y;
-                    x = cmul(x, w);
-                }
-                v[q][r] = x;
-            }
-            dft<R>(v[q], INV);
-            dst[q] = line * ls;
-            dst2[q] = (j - jm) * R + jm;
+            for (int r = 0; r < R; ++r) v[q][r] = load(line[q], j[q] + r * NB);
         }
     }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if (line[q] >= 0) {
+            if constexpr (NS > 1) {
+                const int jm = j[q] % NS;
+#pragma unroll
+                for (int r = 1; r < R; ++r) v[q][r] = twiddle<N, INV>(v[q][r], jm * r * TSTEP, tw);
+            }
+            dft<R>(v[q], INV);
+        }
+    }
+    if (wait) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if (line[q] >= 0) {
+            const int jm = j[q] % NS, dst = (j[q] - jm) * R + jm;
+#pragma unroll
+            for (int r = 0; r < R; ++r) store(line[q], dst + r * NS, v[q][r]);
+        }
+    }
+}
+
+// The last stage of a transform (INV) and the first stage of the opposite one, whose plan is the reverse, so that a
+// thread's outputs of the one are its inputs of the other and stay in registers: v = change(line, element, v,
+// early(line, element)) in between, with the early values on their way meanwhile.  `on`: go on with the
+// second transform.
+template <int R, int N, bool INV, bool COL, int ELEMS, class Load, class Early, class Change, class Store>
+__device__ __forceinline__ void fft_turn(int nlines, float inv_nlines, const double2 *tw, bool on, Load load, Early early,
+                                         Change change, Store store)
+{
+    constexpr int NB = N / R, kPer = (ELEMS / R + kThreads - 1) / kThreads;
+    const int total = nlines * NB;
+    double2 v[kPer][R];
+    decltype(early(0, 0)) e[kPer][R];
+    int line[kPer], j[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int b = (int)threadIdx.x + q * kThreads;
+        line[q] = -1;
+        if (b < total) {
+            butterfly<COL, NB>(b, nlines, inv_nlines, line[q], j[q]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) e[q][r] = early(line[q], j[q] + r * NB);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[q][r] = load(line[q], j[q] + r * NB);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if (line[q] >= 0) {
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[q][r] = twiddle<N, INV>(v[q][r], j[q] * r, tw);
+            dft<R>(v[q], INV);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[q][r] = change(line[q], j[q] + r * NB, v[q][r], e[q][r]);
+            if (on) dft<R>(v[q], !INV);
+        }
+    }
+    if (!on) return;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-        if (dst[q] >= 0) {
+        if (line[q] >= 0) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) buf[dst[q] + pidx<N>(dst2[q] + r * NS)] = v[q][r];
+            for (int r = 0; r < R; ++r) store(line[q], j[q] * R + r, v[q][r]);
         }
     }
-    __syncthreads();
 }
 
-template <int N, int S, bool INV, int ML>
-__device__ __forceinline__ void fft_c(double2 *buf, int ls, int nlines, const double2 *tw)
+// Stages S .. LAST - 1 of a plan, from LDS to LDS.
+template <int N, bool REV, bool INV, bool COL, int ELEMS, int S, int LAST>
+__device__ __forceinline__ void fft_middle(double2 *buf, int ls, int nlines, float inv_nlines, const double2 *tw)
 {
-    if constexpr (S < c_stages(N, ML)) {
-        stage_c<c_radix(N, S, ML), N, c_ns(N, S, ML), INV>(buf, ls, nlines, tw);
-        fft_c<N, S + 1, INV, ML>(buf, ls, nlines, tw);
+    if constexpr (S < LAST) {
+        fft_stage<p_radix<N, REV, S>(), N, p_ns<N, REV, S>(), INV, COL, ELEMS>(
+            nlines, inv_nlines, tw, true, [&](int l, int i) { return buf[l * ls + pidx(i)]; },
+            [&](int l, int i, double2 v) { buf[l * ls + pidx(i)] = v; });
+        __syncthreads();
+        fft_middle<N, REV, INV, COL, ELEMS, S + 1, LAST>(buf, ls, nlines, inv_nlines, tw);
     }
 }
 
-// Transform dispatch: N > 0 selects the compile-time plan for that length, with
-// radices up to 2^ML.
-template <int N, int ML = 4>
-__device__ __forceinline__ void fft_any(double2 *buf, int ls, int nlines, const Plan &P, const double2 *tw, bool inv)
-{
-    if constexpr (N > 0) {
-        if (inv) fft_c<N, 0, true, ML>(buf, ls, nlines, tw);
-        else fft_c<N, 0, false, ML>(buf, ls, nlines, tw);
-    } else {
-        fft_lines(buf, ls, nlines, P, tw, inv);
-    }
-}
+struct Nothing {};
 
 // Tables: forward twiddles exp(-2 pi i m / n) and k^2 = (2 pi m' / n)^2 with m'
 // the signed frequency of index m (the rfft axis x keeps m' = m).
@@ -474,15 +533,15 @@ enum { X_INIT = 0, X_NONLIN = 1, X_FIELD = 2, X_MASK = 3 };
 // (0 < j < n/2), their real bins 0 and n/2 in the two halves of slots 0 and n/2,
 // so a pair needs exactly n slots.  `L` is the number of lines per workgroup
 // (even except in the last workgroup).
-template <int MODE, int N>
+template <int MODE>
 __global__ __launch_bounds__(kThreads) void k_xpass(const double *__restrict__ rin, double2 *spec,
                                                      double *__restrict__ rout, int nx, int nlines_total, int L,
                                                      Plan P, const double2 *__restrict__ tw, double scale,
                                                      const uint8_t *__restrict__ mask_in)
 {
     __shared__ double2 buf[kXPadElems];
-    __shared__ double2 tw_s[N > 0 ? kPadTw : kTwElems];
-    load_twiddles<N>(tw_s, tw, nx);
+    __shared__ double2 tw_s[kTwElems];
+    load_twiddles<0>(tw_s, tw, nx);
     double *bd = reinterpret_cast<double *>(buf);   // bd[2 p] = buf[p].x, bd[2 p + 1] = buf[p].y
     const int hx = nx / 2 + 1, half = nx / 2, ls = nx + nx / 16;
     const int line0 = (int)blockIdx.x * L;
@@ -498,10 +557,10 @@ __global__ __launch_bounds__(kThreads) void k_xpass(const double *__restrict__ r
             nl * nx, [&](int e) { return MODE == X_MASK ? (double)msrc[e] : src[e]; },
             [&](int e, double v) {
                 const int l = fdiv(e, nx, inv_nx), x = e - l * nx;
-                bd[2 * ((l >> 1) * ls + pidx<N>(x)) + (l & 1)] = v;
+                bd[2 * ((l >> 1) * ls + pidx(x)) + (l & 1)] = v;
             });
         if (nl & 1)
-            for (int x = tid; x < nx; x += kThreads) bd[2 * ((nl >> 1) * ls + pidx<N>(x)) + 1] = 0.0;
+            for (int x = tid; x < nx; x += kThreads) bd[2 * ((nl >> 1) * ls + pidx(x)) + 1] = 0.0;
         __syncthreads();
     } else {
         const double2 *src = spec + (size_t)line0 * hx;
@@ -510,14 +569,14 @@ __global__ __launch_bounds__(kThreads) void k_xpass(const double *__restrict__ r
             [&](int e, double2 v) {
                 const int l = fdiv(e, hx, inv_hx), j = e - l * hx;
                 const int base = (l >> 1) * ls;
-                if (j == 0 || j == half) bd[2 * (base + pidx<N>(j)) + (l & 1)] = v.x;
-                else buf[base + pidx<N>((l & 1) ? nx - j : j)] = v;
+                if (j == 0 || j == half) bd[2 * (base + pidx(j)) + (l & 1)] = v.x;
+                else buf[base + pidx((l & 1) ? nx - j : j)] = v;
             });
         if (nl & 1) {                                  // the last pair has no b line
             const int base = (nl >> 1) * ls;
             for (int j = tid; j <= half; j += kThreads) {
-                if (j == 0 || j == half) bd[2 * (base + pidx<N>(j)) + 1] = 0.0;
-                else buf[base + pidx<N>(nx - j)] = make_double2(0.0, 0.0);
+                if (j == 0 || j == half) bd[2 * (base + pidx(j)) + 1] = 0.0;
+                else buf[base + pidx(nx - j)] = make_double2(0.0, 0.0);
             }
         }
         __syncthreads();
@@ -526,35 +585,35 @@ __global__ __launch_bounds__(kThreads) void k_xpass(const double *__restrict__ r
             const float inv_nk = 1.0f / (float)nk;
             for (int e = tid; e < np * nk; e += kThreads) {
                 const int m = fdiv(e, nk, inv_nk), k = 1 + (e - m * nk);
-                const int pa = m * ls + pidx<N>(k), pb = m * ls + pidx<N>(nx - k);
+                const int pa = m * ls + pidx(k), pb = m * ls + pidx(nx - k);
                 const double2 a = buf[pa], b = buf[pb];
                 buf[pa] = make_double2(a.x - b.y, a.y + b.x);
                 buf[pb] = make_double2(a.x + b.y, b.x - a.y);
             }
         }
         __syncthreads();
-        fft_any<N>(buf, ls, np, P, tw_s, true);
+        fft_lines(buf, ls, np, P, tw_s, true);
         if (MODE == X_FIELD) {
             for (int e = tid; e < nl * nx; e += kThreads) {
                 const int l = fdiv(e, nx, inv_nx), x = e - l * nx;
-                rout[(size_t)(line0 + l) * nx + x] = bd[2 * ((l >> 1) * ls + pidx<N>(x)) + (l & 1)] * scale;
+                rout[(size_t)(line0 + l) * nx + x] = bd[2 * ((l >> 1) * ls + pidx(x)) + (l & 1)] * scale;
             }
             return;
         }
         for (int e = tid; e < np * nx; e += kThreads) {
             const int m = fdiv(e, nx, inv_nx), x = e - m * nx;
-            const int p = m * ls + pidx<N>(x);
+            const int p = m * ls + pidx(x);
             const double2 z = buf[p];
             const double a = z.x * scale, b = z.y * scale;
             buf[p] = make_double2(2.0 * a * (1.0 - a) * (1.0 - 2.0 * a), 2.0 * b * (1.0 - b) * (1.0 - 2.0 * b));
         }
         __syncthreads();
     }
-    fft_any<N>(buf, ls, np, P, tw_s, false);
+    fft_lines(buf, ls, np, P, tw_s, false);
     for (int e = tid; e < nl * hx; e += kThreads) {
         const int l = fdiv(e, hx, inv_hx), k = e - l * hx;
         const int base = (l >> 1) * ls;
-        const double2 zk = buf[base + pidx<N>(k)], zr = buf[base + pidx<N>(k == 0 ? 0 : nx - k)];
+        const double2 zk = buf[base + pidx(k)], zr = buf[base + pidx(k == 0 ? 0 : nx - k)];
         spec[(size_t)(line0 + l) * hx + k] = (l & 1) ? make_double2(0.5 * (zk.y + zr.y), -0.5 * (zk.x - zr.x))
                                                      : make_double2(0.5 * (zk.x + zr.x), 0.5 * (zk.y - zr.y));
     }
@@ -577,14 +636,14 @@ __device__ __forceinline__ size_t col_addr(int j, int p, int x, int ny, int hx)
     return AXIS == 1 ? ((size_t)p * ny + j) * hx + x : ((size_t)j * ny + p) * hx + x;
 }
 
-// In-place FFT along y (AXIS 1) or z (AXIS 2) of T-column tiles.
-template <int AXIS, int N>
-__global__ __launch_bounds__(kThreads) void k_colpass(double2 *A, int ny, int hx, int n, int T, int tiles, Plan P,
+// In-place FFT along y of T-column tiles.
+__global__ __launch_bounds__(kThreads) void k_colpass(double2 *A, int ny, int hx, int T, int tiles, Plan P,
                                                        const double2 *__restrict__ tw, int inv)
 {
-    __shared__ double2 buf[N > 0 ? kPadElems : kColElems];
-    __shared__ double2 tw_s[N > 0 ? kPadTw : kTwElems];
-    load_twiddles<N>(tw_s, tw, n);
+    const int n = ny;
+    __shared__ double2 buf[kColElems];
+    __shared__ double2 tw_s[kTwElems];
+    load_twiddles<0>(tw_s, tw, n);
     const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int p = bid / tiles, tile = bid - p * tiles;
     // lines padded to an odd stride: the transposing loads hit distinct banks
@@ -595,17 +654,17 @@ __global__ __launch_bounds__(kThreads) void k_colpass(double2 *A, int ny, int hx
         n * nc,
         [&](int e) {
             const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-            return A[col_addr<AXIS>(j, p, x0 + c, ny, hx)];
+            return A[col_addr<1>(j, p, x0 + c, ny, hx)];
         },
         [&](int e, double2 v) {
             const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-            buf[c * ls + pidx<N>(j)] = v;
+            buf[c * ls + pidx(j)] = v;
         });
     __syncthreads();
-    fft_any<N, kColRadixLog>(buf, ls, nc, P, tw_s, inv != 0);
+    fft_lines(buf, ls, nc, P, tw_s, inv != 0);
     for (int e = tid; e < n * nc; e += kThreads) {
         const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-        A[col_addr<AXIS>(j, p, x0 + c, ny, hx)] = buf[c * ls + pidx<N>(j)];
+        A[col_addr<1>(j, p, x0 + c, ny, hx)] = buf[c * ls + pidx(j)];
     }
 }
 
@@ -615,16 +674,16 @@ enum { Z_INV = 0, Z_INIT = 1, Z_UPDATE = 2 };
 // S = (S - dt k^2 FFT_z(W)) / (1 + dt kappa k^4) (Eq. CH_spectral, evaluated in
 // that order).  With write_w (Z_INIT, Z_UPDATE) W = inverse FFT_z(S) as well, the
 // start of the next step.
-template <int MODE, int N>
+template <int MODE>
 __global__ __launch_bounds__(kThreads) void k_zpass(double2 *S, double2 *W, int ny, int hx, int nz, int T, int tiles,
                                                      Plan P, const double2 *__restrict__ tw,
                                                      const double *__restrict__ kx2, const double *__restrict__ ky2,
                                                      const double *__restrict__ kz2, double dt, double kappa,
                                                      int write_w)
 {
-    __shared__ double2 buf[N > 0 ? kPadElems : kColElems];
-    __shared__ double2 tw_s[N > 0 ? kPadTw : kTwElems];
-    load_twiddles<N>(tw_s, tw, nz);
+    __shared__ double2 buf[kColElems];
+    __shared__ double2 tw_s[kTwElems];
+    load_twiddles<0>(tw_s, tw, nz);
     const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
     const int y = bid / tiles, tile = bid - y * tiles;
     const int x0 = tile * T, nc = min(T, hx - x0), ls = nz + nz / 16 + 1;
@@ -639,11 +698,11 @@ __global__ __launch_bounds__(kThreads) void k_zpass(double2 *S, double2 *W, int 
         },
         [&](int e, double2 v) {
             const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-            buf[c * ls + pidx<N>(j)] = v;
+            buf[c * ls + pidx(j)] = v;
         });
     __syncthreads();
     if (MODE != Z_INV) {
-        fft_any<N>(buf, ls, nc, P, tw_s, false);
+        fft_lines(buf, ls, nc, P, tw_s, false);
         const double dtk = dt * kappa;
         // the old state comes in with U loads in flight per thread (Z_UPDATE);
         // Z_INIT stores the transform as the state
@@ -656,7 +715,7 @@ __global__ __launch_bounds__(kThreads) void k_zpass(double2 *S, double2 *W, int 
             },
             [&](int e, double2 s) {
                 const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-                double2 v = buf[c * ls + pidx<N>(j)];
+                double2 v = buf[c * ls + pidx(j)];
                 if (MODE == Z_UPDATE) {
                     const double k2 = kz2[j] + ky2[y] + kx2[x0 + c];
                     const double den = 1.0 + dtk * k2 * k2;
@@ -664,16 +723,166 @@ __global__ __launch_bounds__(kThreads) void k_zpass(double2 *S, double2 *W, int 
                     v = make_double2((s.x - g * v.x) / den, (s.y - g * v.y) / den);
                 }
                 S[col_addr<2>(j, y, x0 + c, ny, hx)] = v;
-                buf[c * ls + pidx<N>(j)] = v;
+                buf[c * ls + pidx(j)] = v;
             });
         __syncthreads();
         if (!write_w) return;
     }
-    fft_any<N>(buf, ls, nc, P, tw_s, true);
+    fft_lines(buf, ls, nc, P, tw_s, true);
     for (int e = tid; e < nz * nc; e += kThreads) {
         const int j = fdiv(e, nc, inv_nc), c = e - j * nc;
-        W[col_addr<2>(j, y, x0 + c, ny, hx)] = buf[c * ls + pidx<N>(j)];
+        W[col_addr<2>(j, y, x0 + c, ny, hx)] = buf[c * ls + pidx(j)];
     }
+}
+
+// ---------------------------------------------------------------------------
+// The passes of the lengths with a compile-time plan
+// ---------------------------------------------------------------------------
+// As k_xpass, k_colpass and k_zpass, but a line goes to and from memory in the registers of its first and last
+// stages, and where a pass turns from one transform to the opposite one it does so in registers: half of the
+// trips through LDS and of the barriers of a pass that stages whole lines.  Those passes waited on LDS (bank
+// conflicts as many cycles as accesses) with two or three workgroups per CU to hide it.  Bound now by memory: at
+// 384 x 1024 x 1024 the y pass takes 1.49 ms (1.62 before), the x pass 1.50 (2.04), the z pass 3.06 (3.34), that is 4.2
+// to 4.3 TB/s, where a copy of 2 GiB reaches 4.7; a step 7.87 ms (8.75), of 256^3 285 us (349), of 192^3 127
+// (169), of 128 x 64 x 96 35 (44).
+
+// Lines along x, in pairs z = a + i b.  The inverse's first stage builds Z_p from the two half spectra, Z_p = A_p +
+// i B_p and Z_(n-p) = conj A_p + i conj B_p, so each bin is read twice (the second time from a cache).
+template <int MODE, int N>
+__global__ __launch_bounds__(kThreads) void k_xdirect(const double *__restrict__ rin, double2 *spec,
+                                                       double *__restrict__ rout, int nlines_total, int L,
+                                                       const double2 *__restrict__ tw, double scale,
+                                                       const uint8_t *__restrict__ mask_in)
+{
+    constexpr int kStages = c_stages(N, 4), hx = N / 2 + 1, half = N / 2, ls = N + N / 16;
+    constexpr int R0 = p_radix<N, false, 0>();
+    __shared__ double2 buf[kXPadElems];
+    __shared__ double2 tw_s[kPadTw];
+    load_twiddles<N>(tw_s, tw, N);
+    const int line0 = (int)blockIdx.x * L, nl = min(L, nlines_total - line0), np = (nl + 1) >> 1;
+    auto from_lds = [&](int m, int i) { return buf[m * ls + pidx(i)]; };
+    auto to_lds = [&](int m, int i, double2 v) { buf[m * ls + pidx(i)] = v; };
+    if constexpr (MODE == X_INIT || MODE == X_MASK) {
+        fft_stage<R0, N, 1, false, false, kXElems>(
+            np, 0.0f, tw_s, false,
+            [&](int m, int x) {
+                const size_t a = (size_t)(line0 + 2 * m) * N + x, b = a + N;
+                const bool two = 2 * m + 1 < nl;
+                if (MODE == X_MASK) return make_double2((double)mask_in[a], two ? (double)mask_in[b] : 0.0);
+                return make_double2(rin[a], two ? rin[b] : 0.0);
+            },
+            to_lds);
+        __syncthreads();
+    } else {
+        auto from_spectra = [&](int m, int i) {
+            const bool up = i > half;
+            const int k = up ? N - i : i;
+            const double2 *A = spec + (size_t)(line0 + 2 * m) * hx + k;
+            double2 a = A[0], b = 2 * m + 1 < nl ? A[hx] : make_double2(0.0, 0.0);
+            if (k == 0 || k == half) a.y = b.y = 0.0;
+            return up ? make_double2(a.x + b.y, b.x - a.y) : make_double2(a.x - b.y, a.y + b.x);
+        };
+        fft_stage<p_radix<N, true, 0>(), N, 1, true, false, kXElems>(np, 0.0f, tw_s, false, from_spectra, to_lds);
+        __syncthreads();
+        fft_middle<N, true, true, false, kXElems, 1, kStages - 1>(buf, ls, np, 0.0f, tw_s);
+        if constexpr (MODE == X_FIELD) {
+            fft_stage<R0, N, N / R0, true, false, kXElems>(
+                np, 0.0f, tw_s, false, from_lds, [&](int m, int x, double2 v) {
+                    double *a = rout + (size_t)(line0 + 2 * m) * N + x;
+                    a[0] = v.x * scale;
+                    if (2 * m + 1 < nl) a[N] = v.y * scale;
+                });
+            return;
+        } else {
+            fft_turn<R0, N, true, false, kXElems>(
+                np, 0.0f, tw_s, true, from_lds, [](int, int) { return Nothing{}; },
+                [&](int, int, double2 z, Nothing) {
+                    const double a = z.x * scale, b = z.y * scale;
+                    return make_double2(2.0 * a * (1.0 - a) * (1.0 - 2.0 * a), 2.0 * b * (1.0 - b) * (1.0 - 2.0 * b));
+                },
+                to_lds);
+            __syncthreads();
+        }
+    }
+    fft_middle<N, false, false, false, kXElems, 1, kStages>(buf, ls, np, 0.0f, tw_s);
+    for (int e = (int)threadIdx.x; e < nl * hx; e += kThreads) {
+        const int l = e / hx, k = e - l * hx;
+        const double2 zk = from_lds(l >> 1, k), zr = from_lds(l >> 1, k == 0 ? 0 : N - k);
+        spec[(size_t)(line0 + l) * hx + k] = (l & 1) ? make_double2(0.5 * (zk.y + zr.y), -0.5 * (zk.x - zr.x))
+                                                     : make_double2(0.5 * (zk.x + zr.x), 0.5 * (zk.y - zr.y));
+    }
+}
+
+template <int N, bool INV>
+__global__ __launch_bounds__(kThreads) void k_coldirect(double2 *A, int ny, int hx, int T, int tiles,
+                                                         const double2 *__restrict__ tw)
+{
+    constexpr int kStages = c_stages(N, 4), ls = N + N / 16 + 1, RL = p_radix<N, false, kStages - 1>();
+    __shared__ double2 buf[kPadElems];
+    __shared__ double2 tw_s[kPadTw];
+    load_twiddles<N>(tw_s, tw, N);
+    const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
+    const int p = bid / tiles, tile = bid - p * tiles;
+    const int x0 = tile * T, nc = min(T, hx - x0);
+    const float inv_nc = 1.0f / (float)nc;
+    fft_stage<p_radix<N, false, 0>(), N, 1, INV, true, kLdsElems>(
+        nc, inv_nc, tw_s, false, [&](int c, int j) { return A[col_addr<1>(j, p, x0 + c, ny, hx)]; },
+        [&](int c, int j, double2 v) { buf[c * ls + pidx(j)] = v; });
+    __syncthreads();
+    fft_middle<N, false, INV, true, kLdsElems, 1, kStages - 1>(buf, ls, nc, inv_nc, tw_s);
+    fft_stage<RL, N, N / RL, INV, true, kLdsElems>(
+        nc, inv_nc, tw_s, false, [&](int c, int j) { return buf[c * ls + pidx(j)]; },
+        [&](int c, int j, double2 v) { A[col_addr<1>(j, p, x0 + c, ny, hx)] = v; });
+}
+
+template <int MODE, int N>
+__global__ __launch_bounds__(kThreads) void k_zdirect(double2 *S, double2 *W, int ny, int hx, int T, int tiles,
+                                                       const double2 *__restrict__ tw, const double *__restrict__ kx2,
+                                                       const double *__restrict__ ky2, const double *__restrict__ kz2,
+                                                       double dt, double kappa, int write_w)
+{
+    constexpr int kStages = c_stages(N, 4), ls = N + N / 16 + 1, RL = p_radix<N, false, kStages - 1>();
+    constexpr int RI = p_radix<N, true, kStages - 1>();
+    __shared__ double2 buf[kPadElems];
+    __shared__ double2 tw_s[kPadTw];
+    load_twiddles<N>(tw_s, tw, N);
+    const int bid = xcd_order((int)blockIdx.x, (int)gridDim.x);
+    const int y = bid / tiles, tile = bid - y * tiles;
+    const int x0 = tile * T, nc = min(T, hx - x0);
+    const float inv_nc = 1.0f / (float)nc;
+    auto at = [&](int c, int j) { return col_addr<2>(j, y, x0 + c, ny, hx); };
+    auto from_lds = [&](int c, int j) { return buf[c * ls + pidx(j)]; };
+    auto to_lds = [&](int c, int j, double2 v) { buf[c * ls + pidx(j)] = v; };
+    if constexpr (MODE == Z_INV) {
+        fft_stage<p_radix<N, true, 0>(), N, 1, true, true, kLdsElems>(
+            nc, inv_nc, tw_s, false, [&](int c, int j) { return S[at(c, j)]; }, to_lds);
+        __syncthreads();
+    } else {
+        fft_stage<p_radix<N, false, 0>(), N, 1, false, true, kLdsElems>(
+            nc, inv_nc, tw_s, false, [&](int c, int j) { return W[at(c, j)]; }, to_lds);
+        __syncthreads();
+        fft_middle<N, false, false, true, kLdsElems, 1, kStages - 1>(buf, ls, nc, inv_nc, tw_s);
+        const double dtk = dt * kappa, ky = ky2[y];
+        fft_turn<RL, N, false, true, kLdsElems>(
+            nc, inv_nc, tw_s, write_w != 0, from_lds,
+            [&](int c, int j) { return MODE == Z_UPDATE ? S[at(c, j)] : make_double2(0.0, 0.0); },
+            [&](int c, int j, double2 v, double2 s) {
+                if (MODE == Z_UPDATE) {
+                    const double k2 = kz2[j] + ky + kx2[x0 + c];
+                    const double den = 1.0 + dtk * k2 * k2;
+                    const double g = dt * k2;
+                    v = make_double2((s.x - g * v.x) / den, (s.y - g * v.y) / den);
+                }
+                S[at(c, j)] = v;
+                return v;
+            },
+            to_lds);
+        if (!write_w) return;
+        __syncthreads();
+    }
+    fft_middle<N, true, true, true, kLdsElems, 1, kStages - 1>(buf, ls, nc, inv_nc, tw_s);
+    fft_stage<RI, N, N / RI, true, true, kLdsElems>(nc, inv_nc, tw_s, false, from_lds,
+                                                    [&](int c, int j, double2 v) { W[at(c, j)] = v; });
 }
 
 // Radial PSD: per-block partial shell sums in LDS, then a fixed-order sum over
@@ -850,21 +1059,20 @@ void with_length(int n, F &&f)
     }
 }
 
-void enqueue_col(const Geo &G, int axis, double2 *A, const Ptrs &P, bool inv, hipStream_t s)
+// The y pass.
+void enqueue_col(const Geo &G, double2 *A, const Ptrs &P, bool inv, hipStream_t s)
 {
-    if (axis == 1) {
-        if (G.ny == 1) return;
-        with_length(G.ny, [&](auto nc) {
-            hipLaunchKernelGGL((k_colpass<1, decltype(nc)::value>), dim3((unsigned)(G.nz * G.tiles_y)), dim3(kThreads),
-                               0, s, A, G.ny, G.hx, G.ny, G.Ty, G.tiles_y, G.py, P.twy, inv ? 1 : 0);
-        });
-    } else {
-        if (G.nz == 1) return;
-        with_length(G.nz, [&](auto nc) {
-            hipLaunchKernelGGL((k_colpass<2, decltype(nc)::value>), dim3((unsigned)(G.ny * G.tiles_z)), dim3(kThreads),
-                               0, s, A, G.ny, G.hx, G.nz, G.Tz, G.tiles_z, G.pz, P.twz, inv ? 1 : 0);
-        });
-    }
+    if (G.ny == 1) return;
+    with_length(G.ny, [&](auto nc) {
+        constexpr int N = decltype(nc)::value;
+        const dim3 grid((unsigned)(G.nz * G.tiles_y)), block(kThreads);
+        if constexpr (N > 0) {
+            if (inv) hipLaunchKernelGGL((k_coldirect<N, true>), grid, block, 0, s, A, G.ny, G.hx, G.Ty, G.tiles_y, P.twy);
+            else hipLaunchKernelGGL((k_coldirect<N, false>), grid, block, 0, s, A, G.ny, G.hx, G.Ty, G.tiles_y, P.twy);
+        } else {
+            hipLaunchKernelGGL(k_colpass, grid, block, 0, s, A, G.ny, G.hx, G.Ty, G.tiles_y, G.py, P.twy, inv ? 1 : 0);
+        }
+    });
 }
 
 template <int MODE>
@@ -874,8 +1082,13 @@ void enqueue_x(const Geo &G, const double *rin, double2 *spec, double *rout, con
     const int lines = G.nz * G.ny;
     const double scale = 1.0 / ((double)G.nx * (double)G.ny * (double)G.nz);
     with_length(G.nx, [&](auto nc) {
-        hipLaunchKernelGGL((k_xpass<MODE, decltype(nc)::value>), dim3((unsigned)((lines + G.Lx - 1) / G.Lx)),
-                           dim3(kThreads), 0, s, rin, spec, rout, G.nx, lines, G.Lx, G.px, P.twx, scale, mask_in);
+        constexpr int N = decltype(nc)::value;
+        const dim3 grid((unsigned)((lines + G.Lx - 1) / G.Lx)), block(kThreads);
+        if constexpr (N > 0)
+            hipLaunchKernelGGL((k_xdirect<MODE, N>), grid, block, 0, s, rin, spec, rout, lines, G.Lx, P.twx, scale, mask_in);
+        else
+            hipLaunchKernelGGL(k_xpass<MODE>, grid, block, 0, s, rin, spec, rout, G.nx, lines, G.Lx, G.px, P.twx,
+                               scale, mask_in);
     });
 }
 
@@ -883,9 +1096,14 @@ template <int MODE>
 void enqueue_z(const Geo &G, double2 *S, const Ptrs &P, double dt, double kappa, bool write_w, hipStream_t s)
 {
     with_length(G.nz, [&](auto nc) {
-        hipLaunchKernelGGL((k_zpass<MODE, decltype(nc)::value>), dim3((unsigned)(G.ny * G.tiles_z)), dim3(kThreads), 0,
-                           s, S, P.W, G.ny, G.hx, G.nz, G.Tz, G.tiles_z, G.pz, P.twz, P.kx2, P.ky2, P.kz2, dt, kappa,
-                           write_w ? 1 : 0);
+        constexpr int N = decltype(nc)::value;
+        const dim3 grid((unsigned)(G.ny * G.tiles_z)), block(kThreads);
+        if constexpr (N > 0)
+            hipLaunchKernelGGL((k_zdirect<MODE, N>), grid, block, 0, s, S, P.W, G.ny, G.hx, G.Tz, G.tiles_z, P.twz, P.kx2,
+                               P.ky2, P.kz2, dt, kappa, write_w ? 1 : 0);
+        else
+            hipLaunchKernelGGL(k_zpass<MODE>, grid, block, 0, s, S, P.W, G.ny, G.hx, G.nz, G.Tz, G.tiles_z, G.pz, P.twz,
+                               P.kx2, P.ky2, P.kz2, dt, kappa, write_w ? 1 : 0);
     });
 }
 
@@ -982,7 +1200,7 @@ int mc_ch_init(const mc_ch_grid *g, const double *phi0, double *state, void *wor
     int rc = prepare(g, workspace, workspace_bytes, s, &G, &P);
     if (rc) return rc;
     enqueue_x<X_INIT>(G, phi0, P.W, nullptr, P, s);
-    enqueue_col(G, 1, P.W, P, false, s);
+    enqueue_col(G, P.W, P, false, s);
     if (G.nz == 1) {
         HIP_TRY(hipMemcpyAsync(state, P.W, G.spec_elems * sizeof(double2), hipMemcpyDeviceToDevice, s));
     } else {
@@ -1010,9 +1228,9 @@ int mc_ch_steps(const mc_ch_grid *g, int32_t n_steps, double *state, void *works
     if (timed && (rc = ch_time(s, true))) return rc;
     if (n_steps > 0) enqueue_z<Z_INV>(G, S, P, g->dt, g->kappa, true, s);
     for (int32_t i = 0; i < n_steps; ++i) {
-        enqueue_col(G, 1, P.W, P, true, s);
+        enqueue_col(G, P.W, P, true, s);
         enqueue_x<X_NONLIN>(G, nullptr, P.W, nullptr, P, s);
-        enqueue_col(G, 1, P.W, P, false, s);
+        enqueue_col(G, P.W, P, false, s);
         enqueue_z<Z_UPDATE>(G, S, P, g->dt, g->kappa, i + 1 < n_steps, s);
     }
     HIP_TRY(hipGetLastError());
@@ -1035,7 +1253,7 @@ int mc_ch_field(const mc_ch_grid *g, const double *state, double *phi, void *wor
     } else {
         enqueue_z<Z_INV>(G, (double2 *)state, P, g->dt, g->kappa, true, s);
     }
-    enqueue_col(G, 1, P.W, P, true, s);
+    enqueue_col(G, P.W, P, true, s);
     enqueue_x<X_FIELD>(G, nullptr, P.W, phi, P, s);
     HIP_TRY(hipGetLastError());
     return MC_OK;
@@ -1094,7 +1312,7 @@ int mc_mask_psd(const mc_volume *vol, double *psd, void *workspace, size_t works
     if ((rc = prepare(&g, workspace, workspace_bytes, s, &G, &P))) return rc;
     // forward transform of the mask into W: x (from the bytes), y, then z in place
     enqueue_x<X_MASK>(G, nullptr, P.W, nullptr, P, s, vol->mask);
-    enqueue_col(G, 1, P.W, P, false, s);
+    enqueue_col(G, P.W, P, false, s);
     if (G.nz > 1) enqueue_z<Z_INIT>(G, P.W, P, g.dt, g.kappa, false, s);
     const int nb = std::max(G.nx, std::max(G.ny, G.nz)) / 2 + 1;
     hipLaunchKernelGGL(k_psd_partial, dim3(kPsdBlocks), dim3(kThreads), 0, s, (const double2 *)P.W, G.nx, G.ny, G.nz,
