@@ -7,14 +7,14 @@
 // These are scans over the mask, the fluence tally or per-photon records, so they
 // are bound by memory traffic or launch count, not arithmetic: line scans with
 // neighbouring lanes on neighbouring bytes, histograms in LDS, a radix select per
-// slice in one workgroup for the deciles.  The distance transform is separable: a
-// two-sided scan along x, then along y and along z an outward scan from each voxel
+// slice in one workgroup for the deciles.  The distance transform is separable:
+// along x from the packed mask, then along y and along z an outward scan from each voxel
 // over LDS-staged lines that stops, exact, once the squared radius passes the best
 // value; lines it leaves open (far from any solid) are redone by the lower
 // envelope of parabolas of Felzenszwalb & Huttenlocher (2012).  The Spearman
-// correlation compacts each slice's pore voxels, ranks the fluence by one
-// device-wide rocPRIM radix sort of (slice, fluence) keys over just the bits the
-// data occupy, ranks the small integer squared distances by counting in LDS, and
+// correlation compacts each slice's pore voxels, ranks the fluence by
+// buckets in LDS (or by one device-wide rocPRIM radix sort of (slice, fluence) keys over
+// just the bits the data occupy), ranks the small integer squared distances by counting in LDS, and
 // averages tied ranks.
 #include <hip/hip_runtime.h>
 
@@ -23,6 +23,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_segmented_radix_sort.hpp>
@@ -59,6 +60,9 @@ __device__ __forceinline__ size_t line_elem(int axis, long long l, int j, int nx
     }
     return (size_t)l * nx + j;                                                     // l = z * ny + y
 }
+
+// distance of a squared distance
+__device__ __forceinline__ double edt_distance(int d2) { return d2 >= kInf ? INFINITY : sqrt((double)d2); }
 
 // One thread per line; the workgroup counts its chords in an LDS histogram of
 // 2 (n + 1) words and adds the non-zero bins to the global one at the end (global
@@ -332,6 +336,24 @@ __device__ __forceinline__ unsigned int block_inclusive_scan(unsigned int v, uns
     return v + before;
 }
 
+// Every voxel i of a slice of n once, kTopBatch loads in flight a thread (one workgroup a
+// slice waits on its loads: 187 slices of 256 x 256 took 168 us with one load at a time and
+// barriers in the last pass also where no tie is cut, now 79); whole wavefronts call
+// visit(i, key) together, also with i >= n (the key is then any).
+constexpr int kTopBatch = 8;
+
+template <class Visit>
+__device__ __forceinline__ void for_keys(const long long *f, long long n, Visit visit)
+{
+    for (long long i0 = (long long)threadIdx.x; i0 - (long long)threadIdx.x < n; i0 += kTopBatch * kTopThreads) {
+        long long v[kTopBatch];
+#pragma unroll
+        for (int j = 0; j < kTopBatch; ++j) v[j] = f[min(i0 + j * kTopThreads, n - 1)];
+#pragma unroll
+        for (int j = 0; j < kTopBatch; ++j) visit(i0 + j * kTopThreads, tally_key(v[j]));
+    }
+}
+
 __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__restrict__ F, const uint8_t *__restrict__ mask,
                                                           long long n, int z0, long long k, long long *top_count,
                                                           long long *top_solid)
@@ -354,11 +376,12 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
     __syncthreads();
     {
         unsigned long long lo = ~0ull, hi = 0ull;
-        for (long long i = t; i < n; i += kTopThreads) {
-            const unsigned long long key = tally_key(f[i]);
-            lo = min(lo, key);
-            hi = max(hi, key);
-        }
+        for_keys(f, n, [&](long long i, unsigned long long key) {
+            if (i < n) {
+                lo = min(lo, key);
+                hi = max(hi, key);
+            }
+        });
         for (int o = 32; o > 0; o >>= 1) {
             lo = min(lo, (unsigned long long)__shfl_xor(lo, o));
             hi = max(hi, (unsigned long long)__shfl_xor(hi, o));
@@ -373,7 +396,7 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
     // bits at and above `top` are resolved: they equal those of `prefix`
     int top = diff ? 64 - __clzll((long long)diff) : 0;
     unsigned long long prefix = top >= 64 ? 0ull : (s_min & (~0ull << top));
-    long long kk = k;
+    long long kk = k, equal = n;
     bool in_lds = false;
     while (top > 0) {
         const int bits = min(kTopBits, top), sh = top - bits, nb = 1 << bits;
@@ -387,13 +410,9 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
                 if ((key & hi_mask) == prefix) atomicAdd(&h[(key >> sh) & (unsigned long long)(nb - 1)], 1u);
             }
         } else {
-            for (long long i0 = 0; i0 < n; i0 += kTopThreads) {
-                const long long i = i0 + t;
+            for_keys(f, n, [&](long long i, unsigned long long key) {
                 int d = -1;
-                if (i < n) {
-                    const unsigned long long key = tally_key(f[i]);
-                    if ((key & hi_mask) == prefix) d = (int)((key >> sh) & (unsigned long long)(nb - 1));
-                }
+                if (i < n && (key & hi_mask) == prefix) d = (int)((key >> sh) & (unsigned long long)(nb - 1));
                 // a wave whose candidates share one digit adds them with one atomic
                 const int d0 = __shfl(d, 0);
                 if (__ballot(d == d0) == ~0ull) {
@@ -401,7 +420,7 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
                 } else if (d >= 0) {
                     atomicAdd(&h[d], 1u);
                 }
-            }
+            });
         }
         __syncthreads();
         // thread t holds digits nb-1-2t and nb-2-2t: the prefix over threads runs from the top digit down
@@ -419,18 +438,13 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
         __syncthreads();
         prefix = s_prefix;
         kk = s_k;
+        equal = s_count;
         top = sh;
         if (!in_lds && top > 0 && s_count <= (unsigned int)kTopCand) {
             // the keys still in the running fit in LDS: copy them there (any order)
             const unsigned long long keep = ~0ull << top;
-            for (long long i0 = 0; i0 < n; i0 += kTopThreads) {
-                const long long i = i0 + t;
-                unsigned long long key = 0ull;
-                bool match = false;
-                if (i < n) {
-                    key = tally_key(f[i]);
-                    match = (key & keep) == prefix;
-                }
+            for_keys(f, n, [&](long long i, unsigned long long key) {
+                const bool match = i < n && (key & keep) == prefix;
                 const unsigned long long bal = __ballot(match);
                 if (bal) {
                     unsigned int at = 0u;
@@ -438,33 +452,38 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
                     at = __shfl(at, 0);
                     if (match) cand[at + __popcll(bal & ((1ull << lane) - 1ull))] = key;
                 }
-            }
+            });
             in_lds = true;
             __syncthreads();
         }
     }
     const unsigned long long T = prefix;
     const long long need = kk;
-    long long run = 0;
     unsigned int solid = 0;
-    for (long long i0 = 0; i0 < n; i0 += kTopThreads) {
-        const long long i = i0 + t;
-        unsigned long long key = 0ull;
-        if (i < n) key = tally_key(f[i]);
-        const bool eq = i < n && key == T;
-        const unsigned long long bal = __ballot(eq);
-        if (lane == 0) wsum[wave] = (unsigned int)__popcll(bal);
-        __syncthreads();
-        long long off = run + __popcll(bal & ((1ull << lane) - 1ull));
-        long long tot = 0;
-        for (int w = 0; w < kTopThreads / 64; ++w) {
-            if (w < wave) off += wsum[w];
-            tot += wsum[w];
+    if (need == equal) {
+        // all the voxels equal to T are taken
+        for_keys(f, n, [&](long long i, unsigned long long key) { solid += (i < n && key >= T && m[i] == 0) ? 1u : 0u; });
+    } else {
+        long long run = 0;
+        for (long long i0 = 0; i0 < n; i0 += kTopThreads) {
+            const long long i = i0 + t;
+            unsigned long long key = 0ull;
+            if (i < n) key = tally_key(f[i]);
+            const bool eq = i < n && key == T;
+            const unsigned long long bal = __ballot(eq);
+            if (lane == 0) wsum[wave] = (unsigned int)__popcll(bal);
+            __syncthreads();
+            long long off = run + __popcll(bal & ((1ull << lane) - 1ull));
+            long long tot = 0;
+            for (int w = 0; w < kTopThreads / 64; ++w) {
+                if (w < wave) off += wsum[w];
+                tot += wsum[w];
+            }
+            const bool take = i < n && (key > T || (eq && off < need));
+            solid += (take && m[i] == 0) ? 1u : 0u;
+            run += tot;
+            __syncthreads();
         }
-        const bool take = i < n && (key > T || (eq && off < need));
-        solid += (take && m[i] == 0) ? 1u : 0u;
-        run += tot;
-        __syncthreads();
     }
     for (int o = 32; o > 0; o >>= 1) solid += __shfl_xor(solid, o);
     if (lane == 0) wsum[wave] = solid;
@@ -477,8 +496,8 @@ __global__ __launch_bounds__(kTopThreads) void k_slice_top(const long long *__re
     }
 }
 
-// Distance transform, pass 1: squared distance along x to the nearest solid
-// voxel of the same line, kInf where the line has none.  One wavefront per line,
+// Distance transform, pass 1 where the y-lines are too long for tiles: squared distance
+// along x to the nearest solid voxel of the same line, kInf where the line has none.  One wavefront per line,
 // lane = x within a 64-voxel chunk: an inclusive max-scan across the lanes of
 // "x if solid" (carried from chunk to chunk) gives the nearest solid voxel on the
 // left, a min-scan from the right end the nearest on the right; every load and
@@ -522,6 +541,45 @@ __global__ __launch_bounds__(kThreads) void k_edt_x(const uint8_t *__restrict__ 
             o[x] = d == kInf ? kInf : d * d;
         }
     }
+}
+
+// The mask packed 32 voxels of an x-line to a word, 1 for solid, nw = ceil(nx / 32)
+// words a line; one wavefront packs 64 voxels at a time.  Also clears the counts of open
+// lines of the two passes.
+__global__ __launch_bounds__(kThreads) void k_edt_bits(const uint8_t *__restrict__ mask, int nx, int nw, long long lines,
+                                                       unsigned int *__restrict__ bits, int *count_y, int *count_z)
+{
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count_y = *count_z = 0;
+    const int lane = (int)(threadIdx.x & 63);
+    const long long waves = (long long)gridDim.x * (kThreads / 64);
+    for (long long l = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); l < lines; l += waves) {
+        const uint8_t *m = mask + (size_t)l * nx;
+        for (int x0 = 0; x0 < nx; x0 += 64) {
+            const int x = x0 + lane;
+            const unsigned long long solid = __ballot(x < nx && m[x] == 0);
+            const int w = (x0 >> 5) + lane;
+            if (lane < 2 && w < nw) bits[(size_t)l * nw + w] = (unsigned int)(solid >> (32 * lane));
+        }
+    }
+}
+
+// Squared distance along x from voxel x to the nearest solid voxel of its line, whose
+// packed words are b[0 .. nw); kInf where the line has none.
+__device__ __forceinline__ int edt_x2(const unsigned int *b, int nw, int x)
+{
+    const int w = x >> 5, o = x & 31;
+    const unsigned int here = b[w], prev = w > 0 ? b[w - 1] : 0u, next = w + 1 < nw ? b[w + 1] : 0u;
+    int d = kInf;
+    // x and the 32 to 63 voxels on either side; words beyond while they can still be nearer
+    const unsigned long long left = ((unsigned long long)here << 32 | prev) << (31 - o);      // bit 63: x itself
+    const unsigned long long right = ((unsigned long long)next << 32 | here) >> o;            // bit 0: x itself
+    if (left) d = __clzll((long long)left);
+    if (right) d = min(d, __ffsll(right) - 1);
+    for (int u = w - 2; u >= 0 && x - 32 * u - 31 < d; --u)
+        if (b[u]) d = min(d, x - 32 * u - 31 + __clz((int)b[u]));
+    for (int u = w + 2; u < nw && 32 * u - x < d; ++u)
+        if (b[u]) d = min(d, 32 * u - x + __ffs((int)b[u]) - 1);
+    return d == kInf ? kInf : d * d;
 }
 
 // Passes 2 and 3: along y (axis 1) or z (axis 2), f(q) -> min_p f(p) + (q - p)^2
@@ -575,22 +633,27 @@ __global__ __launch_bounds__(kThreads) void k_edt_scan(const int *__restrict__ i
 
 // The same scan with the lines staged in LDS: a workgroup takes tx consecutive
 // x-columns of the n voxels along AXIS at one position of the remaining axis (z for
-// y-lines, y for z-lines), loads them once with coalesced runs of tx words, and
-// scans there; candidates, early stop and open-line marks are those of k_edt_scan,
-// so the results are the same.  The tile is [n][tx] words, tx a power of two.  On
-// the 256^3 workload narrow tiles (more workgroups per CU) measured fastest for
-// the whole transform: 0.42 ms at 8 columns, 0.45 at 16, 0.57 at 32, 0.86 at 64,
-// against 0.67 ms for the scan from global memory.
-#ifndef MC_EDT_TILE_X
-#define MC_EDT_TILE_X 8
-#endif
-constexpr int kEdtTileX = MC_EDT_TILE_X;
+// y-lines, y for z-lines) and scans there; early stop and open lines are those of
+// k_edt_scan, so the results are the same (a candidate beyond the end of the line is
+// replaced by the end voxel at that distance, which costs no less than the end voxel
+// itself).  The y pass forms its input from the packed mask, the z pass writes what the
+// caller wants of the result, so the transform moves 1 byte in, 4 out, 4 in and 4 or 8
+// out per voxel.  A tile is [n][tx] words, 32 columns (whole 128-byte lines of memory)
+// where its lines fit: with 8 columns of 256-voxel lines each line of memory went to the
+// L2 of four XCDs.  256^3, wavelength 24: mask packed in 19 us, y pass 104, z pass 67 (81
+// to distances), against 74 for an x pass, 168, 125 and 33 for the distances with tiles of
+// 8 columns and an x pass of its own.  What is left is the scan's arithmetic: the lanes of
+// a wavefront go as far as the farthest of them.
+constexpr int kEdtTileX = 32;
 constexpr int kEdtTileWords = 16384;       // 64 KB of LDS
+constexpr int kEdtMaskWords = 8192;        // 32 KB: the packed plane, where it is as small
+constexpr int kEdtTileThreads = 1024;
 
-template <int AXIS>
-__global__ __launch_bounds__(kThreads) void k_edt_tile(const int *__restrict__ in, int *__restrict__ out,
-                                                       uint8_t *__restrict__ open_line, int nx, int ny, int nz,
-                                                       int tx_log)
+template <int AXIS, typename Out>
+__global__ __launch_bounds__(kEdtTileThreads) void k_edt_tile(const int *__restrict__ in,
+                                                              const unsigned int *__restrict__ bits, int nw,
+                                                              Out *__restrict__ out, int *__restrict__ list,
+                                                              int *__restrict__ count, int nx, int ny, int nz, int tx_log)
 {
     extern __shared__ int tile[];
     const int n = AXIS == 1 ? ny : nz;
@@ -600,36 +663,51 @@ __global__ __launch_bounds__(kThreads) void k_edt_tile(const int *__restrict__ i
     const long long base = (AXIS == 1 ? (long long)other * nx * ny : (long long)other * nx) + x0;
     const int w = min(tx, nx - x0);
     const int cells = n << tx_log;
-    for (int e = (int)threadIdx.x; e < cells; e += kThreads) {
-        const int q = e >> tx_log, c = e & (tx - 1);
-        if (c < w) tile[e] = in[base + q * stride + c];
+    if constexpr (AXIS == 1) {
+        const unsigned int *plane = bits + (size_t)other * ny * nw;
+        if ((long long)n * nw <= kEdtMaskWords) {
+            unsigned int *staged = (unsigned int *)(tile + cells);
+            for (int i = (int)threadIdx.x; i < n * nw; i += kEdtTileThreads) staged[i] = plane[i];
+            __syncthreads();
+            for (int e = (int)threadIdx.x; e < cells; e += kEdtTileThreads)
+                if (x0 + (e & (tx - 1)) < nx) tile[e] = edt_x2(staged + (e >> tx_log) * nw, nw, x0 + (e & (tx - 1)));
+        } else {
+            for (int e = (int)threadIdx.x; e < cells; e += kEdtTileThreads)
+                if (x0 + (e & (tx - 1)) < nx)
+                    tile[e] = edt_x2(plane + (size_t)(e >> tx_log) * nw, nw, x0 + (e & (tx - 1)));
+        }
+    } else {
+#pragma unroll 8
+        for (int e = (int)threadIdx.x; e < cells; e += kEdtTileThreads) {
+            const int c = e & (tx - 1);
+            if (c < w) tile[e] = in[base + (e >> tx_log) * stride + c];
+        }
     }
     __syncthreads();
-    for (int e = (int)threadIdx.x; e < cells; e += kThreads) {
+    unsigned int open = 0u;                 // bit c where a voxel of column c stays open
+    for (int e = (int)threadIdx.x; e < cells; e += kEdtTileThreads) {
         const int q = e >> tx_log, c = e & (tx - 1);
         if (c >= w) continue;
         int best = tile[e];
-        bool done = false;
-        for (int r = 1; r <= kEdtReach + 1; ++r) {
-            const int r2 = r * r;
-            const bool lo = q - r >= 0, hi = q + r < n;
-            if (r2 >= best || (!lo && !hi)) {
-                done = true;
-                break;
-            }
-            if (r > kEdtReach) break;
-            if (lo) {
-                const int v = tile[e - (r << tx_log)];
-                if (v < kInf) best = std::min(best, v + r2);
-            }
-            if (hi) {
-                const int v = tile[e + (r << tx_log)];
-                if (v < kInf) best = std::min(best, v + r2);
-            }
+        const int far = max(q, n - 1 - q), reach = min(far, kEdtReach);
+        // two distances a turn: one too far costs nothing but its look
+        int r = 1;
+        for (; r <= reach && r * r < best; r += 2) {
+            const int lo = tile[(max(q - r, 0) << tx_log) + c], hi = tile[(min(q + r, n - 1) << tx_log) + c];
+            const int lo2 = tile[(max(q - r - 1, 0) << tx_log) + c], hi2 = tile[(min(q + r + 1, n - 1) << tx_log) + c];
+            best = min(best, min(min(lo, hi) + r * r, min(lo2, hi2) + (r + 1) * (r + 1)));
         }
-        out[base + q * stride + c] = best;
-        if (!done) open_line[(long long)other * nx + x0 + c] = 1;
+        if constexpr (std::is_same<Out, double>::value) out[base + q * stride + c] = edt_distance(best);
+        else out[base + q * stride + c] = best;
+        if (r <= far && r * r < best) open |= 1u << c;
     }
+    if (!__syncthreads_or((int)open)) return;
+    if (threadIdx.x == 0) tile[0] = 0;
+    __syncthreads();
+    atomicOr((unsigned int *)tile, open);
+    __syncthreads();
+    if ((int)threadIdx.x < w && (((unsigned int)tile[0] >> threadIdx.x) & 1u))
+        list[atomicAdd(count, 1)] = (int)((long long)other * nx + x0 + (int)threadIdx.x);
 }
 
 // the tile width for lines of n voxels: the widest power of two up to kEdtTileX (and
@@ -661,8 +739,10 @@ __global__ void k_edt_clear(uint8_t *open_line, long long lines, int *count)
 // Lower envelope of the parabolas rooted at the finite in(p) of the listed lines,
 // one thread per line; scratch arrays laid out [k][slot] so that neighbouring
 // threads touch neighbouring words; C slots, a thread takes lines t, t + C, ...
-__global__ void k_edt_env(const int *__restrict__ in, int *__restrict__ out, int axis, int n, const int *list,
-                          const int *count, long long C, int nx, int ny, int *sv, int *sf, double *sz)
+// The input is `in`, or the packed mask (in null, axis 1).
+template <typename Out>
+__global__ void k_edt_env(const int *__restrict__ in, const unsigned int *__restrict__ bits, int nw,
+                          Out *__restrict__ out, int axis, int n, const int *list, const int *count, long long C, int nx, int ny, int *sv, int *sf, double *sz)
 {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= C) return;
@@ -670,11 +750,16 @@ __global__ void k_edt_env(const int *__restrict__ in, int *__restrict__ out, int
     auto F = [&](int k) -> int & { return sf[(size_t)k * C + t]; };
     auto Z = [&](int k) -> double & { return sz[(size_t)k * C + t]; };
     const long long cnt = *count;
+    auto put = [&](long long l, int q, int d2) {
+        if constexpr (std::is_same<Out, double>::value) out[line_elem(axis, l, q, nx, ny)] = edt_distance(d2);
+        else out[line_elem(axis, l, q, nx, ny)] = d2;
+    };
     for (long long idx = t; idx < cnt; idx += C) {
         const long long l = list[idx];
         int k = -1;
         for (int q = 0; q < n; ++q) {
-            const int fq = in[line_elem(axis, l, q, nx, ny)];
+            const int fq = in ? in[line_elem(axis, l, q, nx, ny)]
+                              : edt_x2(bits + ((size_t)(l / nx) * ny + q) * nw, nw, (int)(l % nx));
             if (fq >= kInf) continue;
             if (k < 0) {
                 k = 0;
@@ -698,14 +783,14 @@ __global__ void k_edt_env(const int *__restrict__ in, int *__restrict__ out, int
             Z(k + 1) = INFINITY;
         }
         if (k < 0) {                    // no solid voxel reaches this line
-            for (int q = 0; q < n; ++q) out[line_elem(axis, l, q, nx, ny)] = kInf;
+            for (int q = 0; q < n; ++q) put(l, q, kInf);
             continue;
         }
         int j = 0;
         for (int q = 0; q < n; ++q) {
             while (Z(j + 1) < (double)q) ++j;
             const int d = q - V(j);
-            out[line_elem(axis, l, q, nx, ny)] = d * d + F(j);
+            put(l, q, d * d + F(j));
         }
     }
 }
@@ -713,8 +798,7 @@ __global__ void k_edt_env(const int *__restrict__ in, int *__restrict__ out, int
 __global__ void k_edt_out(const int *__restrict__ g, long long n, double *dist)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int d = g[i];
-        dist[i] = d >= kInf ? INFINITY : sqrt((double)d);
+        dist[i] = edt_distance(g[i]);
     }
 }
 
@@ -776,7 +860,10 @@ __global__ __launch_bounds__(kSpThreads) void k_offsets(const int *__restrict__ 
         if (threadIdx.x == kSpThreads - 1) s_carry = incl;
         __syncthreads();
     }
-    if (threadIdx.x == 0) stats[0] = (unsigned long long)s_carry;
+    if (threadIdx.x == 0) {
+        stats[0] = (unsigned long long)s_carry;
+        stats[3] = 0ull;
+    }
 }
 
 __global__ __launch_bounds__(kSpThreads) void k_compact(const uint8_t *__restrict__ mask, const long long *__restrict__ F,
@@ -856,6 +943,205 @@ __global__ __launch_bounds__(kSpThreads) void k_chunk_max(const unsigned long lo
         unsigned long long v = 0ull;
         for (int w = 0; w < kSpThreads / 64; ++w) v = max(v, wmax[threadIdx.x][w]);
         stats[1 + threadIdx.x] = v;
+    }
+}
+
+// Ranks of a slice's fluence by buckets, one workgroup a slice: the range of its keys is
+// cut into 2^14 equal buckets (a bucket of its own for the smallest key, which many voxels
+// share where few photons come); as many buckets at a time as LDS holds keys of, the keys
+// are put in bucket order there, the rank of each (the start of its bucket plus the keys
+// below it and half of those equal to it in it) takes its place, and the keys fetch their
+// ranks.
+//
+// Bound by the sweeps over the slice by one workgroup (two to count, two for each 11264
+// keys) and the LDS reads of the comparisons, some 10 a key.  256^3, 187 slices of 46e3
+// pore voxels: 260 us, against 880 for a device-wide sort of (slice, fluence) keys with
+// its passes before and after.  (Buckets in memory instead of LDS: 340 us, for 8.7e6
+// scattered 8-byte stores.)
+constexpr int kBuckets = (1 << 14) + 1;
+constexpr int kBucketKeys = 11264;             // with the bucket counts 152 KB of LDS
+constexpr int kBucketBatch = 8;
+constexpr long long kBucketCompares = 64;      // a key, on average
+constexpr long long kBucketSlice = 65536;      // six turns at most
+constexpr int kBucketSlices = 64;
+
+// A key's bucket never falls as the key grows: the conversion, the product and the
+// truncation each keep the order.
+struct Buckets {
+    long long lo;
+    double scale;
+    __device__ __forceinline__ int of(long long key) const
+    {
+        const double at = (double)((unsigned long long)key - (unsigned long long)lo) * scale;
+        return key == lo ? 0 : 1 + min((int)at, kBuckets - 2);
+    }
+};
+
+// Every key of [b, e) once, kBucketBatch loads in flight a thread.
+template <typename T, class Visit>
+__device__ __forceinline__ void for_slice(const T *key, int b, int e, Visit visit)
+{
+    const unsigned n = (unsigned)(e - b);
+    for (unsigned i0 = threadIdx.x; i0 < n; i0 += kBucketBatch * kSpThreads) {
+        T v[kBucketBatch];
+#pragma unroll
+        for (int j = 0; j < kBucketBatch; ++j) v[j] = key[b + (int)min(i0 + j * kSpThreads, n - 1u)];
+#pragma unroll
+        for (int j = 0; j < kBucketBatch; ++j)
+            if (i0 + j * kSpThreads < n) visit(b + (int)(i0 + j * kSpThreads), v[j]);
+    }
+}
+
+// The same over two arrays: a load inside a visit would wait by itself.
+template <typename T, typename U, class Visit>
+__device__ __forceinline__ void for_slice(const T *key, const U *other, int b, int e, Visit visit)
+{
+    const unsigned n = (unsigned)(e - b);
+    for (unsigned i0 = threadIdx.x; i0 < n; i0 += kBucketBatch * kSpThreads) {
+        T v[kBucketBatch];
+        U w[kBucketBatch];
+#pragma unroll
+        for (int j = 0; j < kBucketBatch; ++j) {
+            const int i = b + (int)min(i0 + j * kSpThreads, n - 1u);
+            v[j] = key[i];
+            w[j] = other[i];
+        }
+#pragma unroll
+        for (int j = 0; j < kBucketBatch; ++j)
+            if (i0 + j * kSpThreads < n) visit(b + (int)(i0 + j * kSpThreads), v[j], w[j]);
+    }
+}
+
+// Sets *skipped, and leaves the slice, where its keys would take more than kBucketCompares
+// comparisons each or a bucket holds more than kBucketKeys.
+__global__ __launch_bounds__(kSpThreads) void k_bucket_rank(const long long *__restrict__ key, const int *__restrict__ begin,
+                                                            const int *__restrict__ end, uint16_t *bucket, int *slot,
+                                                            double *__restrict__ rank, unsigned long long *skipped)
+{
+    __shared__ unsigned int P[kBuckets + 1];
+    __shared__ long long held[kBucketKeys];
+    __shared__ unsigned int wsum[kSpThreads / 64];
+    __shared__ long long s_lo[kSpThreads / 64], s_hi[kSpThreads / 64];
+    __shared__ unsigned long long s_work;
+    __shared__ unsigned int s_most;
+    const int b = begin[blockIdx.x], e = end[blockIdx.x], t = (int)threadIdx.x;
+    if (b == e) return;
+    for (int i = t; i < kBuckets; i += kSpThreads) P[i] = 0u;
+    if (t == 0) {
+        s_work = 0ull;
+        s_most = 0u;
+    }
+    long long lo = 0x7fffffffffffffffll, hi = -0x7fffffffffffffffll - 1;
+    for_slice(key, b, e, [&](int, long long v) {
+        lo = min(lo, v);
+        hi = max(hi, v);
+    });
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (long long)__shfl_xor(lo, o));
+        hi = max(hi, (long long)__shfl_xor(hi, o));
+    }
+    if ((t & 63) == 0) {
+        s_lo[t >> 6] = lo;
+        s_hi[t >> 6] = hi;
+    }
+    __syncthreads();
+    for (int w = 0; w < kSpThreads / 64; ++w) {
+        lo = min(lo, s_lo[w]);
+        hi = max(hi, s_hi[w]);
+    }
+    // a range below the number of buckets gives each value its own
+    const double range = (double)((unsigned long long)hi - (unsigned long long)lo);
+    const Buckets B{lo, fmin(1.0, (double)(kBuckets - 2) / range)};
+    for_slice(key, b, e, [&](int i, long long v) {
+        const int u = B.of(v);
+        bucket[i] = (uint16_t)u;
+        atomicAdd(&P[u], 1u);
+    });
+    __syncthreads();
+    // exclusive scan: thread t takes the run [r0, r1)
+    constexpr int per = (kBuckets + kSpThreads - 1) / kSpThreads;
+    const int r0 = min(t * per, kBuckets), r1 = min(r0 + per, kBuckets);
+    unsigned int sum = 0u, most = 0u;
+    unsigned long long work = 0ull;
+    for (int i = r0; i < r1; ++i) {
+        const unsigned int c = P[i];
+        sum += c;
+        if (i > 0) {
+            work += (unsigned long long)c * c;
+            most = max(most, c);
+        }
+    }
+    atomicAdd(&s_work, work);
+    atomicMax(&s_most, most);
+    unsigned int run = block_inclusive_scan(sum, wsum) - sum;
+    if (s_work > (unsigned long long)(kBucketCompares * (e - b)) || s_most > (unsigned int)kBucketKeys) {
+        if (t == 0) *skipped = 1ull;
+        return;
+    }
+    for (int i = r0; i < r1; ++i) {
+        const unsigned int c = P[i];
+        P[i] = run;
+        run += c;
+    }
+    if (t == 0) P[kBuckets] = (unsigned int)(e - b);
+    __syncthreads();
+    const unsigned int first = P[1];           // keys equal to lo
+    __syncthreads();
+    for_slice(bucket, b, e, [&](int i, int u) {
+        if (u == 0) rank[i] = 0.5 * (double)(first + 1u);
+    });
+    // buckets [u0, u1) at a time, base keys lie before them
+    unsigned int base = first;
+    for (int u0 = 1; u0 < kBuckets && base < (unsigned int)(e - b);) {
+        int u1 = u0 + 1, top = kBuckets;       // P[u1] - base <= kBucketKeys
+        while (u1 < top) {
+            const int mid = (u1 + top + 1) >> 1;
+            if (P[mid] - base <= (unsigned int)kBucketKeys) u1 = mid;
+            else top = mid - 1;
+        }
+        const unsigned int next = P[u1];
+        __syncthreads();
+        for_slice(bucket, key, b, e, [&](int i, int u, long long v) {
+            if (u >= u0 && u < u1) {
+                const int at = (int)(atomicAdd(&P[u], 1u) - base);
+                held[at] = v;
+                slot[i] = at;
+            }
+        });
+        __syncthreads();                       // P[u] is now the end of bucket u of these
+        // in bucket order: neighbouring lanes look at the same few keys
+        const unsigned int n = next - base;
+        double r[(kBucketKeys + kSpThreads - 1) / kSpThreads];
+#pragma unroll
+        for (int j = 0; j < (kBucketKeys + kSpThreads - 1) / kSpThreads; ++j) {
+            const unsigned int at = (unsigned int)t + (unsigned int)j * kSpThreads;
+            r[j] = 0.0;
+            if (at < n) {
+                const long long v = held[at];
+                const int u = B.of(v);
+                const unsigned int p0 = u == u0 ? base : P[u - 1], p1 = P[u];
+                unsigned int below = 0u, equal = 0u;
+                for (unsigned int p = p0 - base; p < p1 - base; ++p) {
+                    const long long o = held[p];
+                    below += o < v ? 1u : 0u;
+                    equal += o == v ? 1u : 0u;
+                }
+                r[j] = (double)(p0 + below) + 0.5 * (double)(equal + 1u);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < (kBucketKeys + kSpThreads - 1) / kSpThreads; ++j) {
+            const unsigned int at = (unsigned int)t + (unsigned int)j * kSpThreads;
+            if (at < n) held[at] = __double_as_longlong(r[j]);
+        }
+        __syncthreads();
+        for_slice(bucket, slot, b, e, [&](int i, int u, int at) {
+            if (u >= u0 && u < u1) rank[i] = __longlong_as_double(held[at]);
+        });
+        __syncthreads();
+        base = next;
+        u0 = u1;
     }
 }
 
@@ -1027,38 +1313,62 @@ EdtScratch edt_layout(const mc_volume *vol, void *ws)
     return e;
 }
 
-// squared distances (int, kInf where no solid voxel exists) into e.g
-int enqueue_sqdist(const mc_volume *vol, const EdtScratch &e, hipStream_t s)
+// Squared distances (int, kInf where no solid voxel exists) into e.g, or, where dist is
+// given, distances into dist.  Lines too long for a tile in LDS are scanned in memory.
+int enqueue_sqdist(const mc_volume *vol, const EdtScratch &e, double *dist, hipStream_t s)
 {
     const int nx = vol->nx, ny = vol->ny, nz = vol->nz;
-    const long long xl = (long long)ny * nz;
+    const long long xl = (long long)ny * nz, n = (long long)nx * xl;
     const dim3 grid((unsigned)std::min<long long>(1024, ((long long)nx * ny + kThreads - 1) / kThreads), (unsigned)nz);
-    hipLaunchKernelGGL(k_edt_x, dim3((unsigned)((xl + kThreads / 64 - 1) / (kThreads / 64))), dim3(kThreads), 0, s,
-                       vol->mask, nx, xl, e.g);
+    const unsigned line_blocks = (unsigned)((xl + kThreads / 64 - 1) / (kThreads / 64));
     const unsigned env_grid = (unsigned)((e.C + kThreads - 1) / kThreads);
-    // y: g -> h, z: h -> g
-    for (int axis = 1; axis <= 2; ++axis) {
-        const int *in = axis == 1 ? e.g : e.h;
-        int *out = axis == 1 ? e.h : e.g;
-        const int n = axis == 1 ? ny : nz;
-        const long long lines = (long long)nx * (axis == 1 ? nz : ny);
+    auto tiles = [&](int lg, int others) { return dim3((unsigned)((nx + (1 << lg) - 1) >> lg), (unsigned)others); };
+    auto lds = [](int lg, int len) { return sizeof(int) * ((size_t)len << lg); };
+    // x and y: e.h.  The packed mask lies in e.g, which holds nothing until the z pass.
+    const int ly = edt_tile_log(ny, nx), lz = edt_tile_log(nz, nx);
+    const int nw = (nx + 31) / 32;
+    unsigned int *bits = (unsigned int *)e.g;
+    int *count_z = (int *)e.open;           // the marks are only used with scans in memory
+    if (ly >= 0) {
+        hipLaunchKernelGGL(k_edt_bits, dim3(std::min(line_blocks, 4096u)), dim3(kThreads), 0, s, vol->mask, nx, nw, xl,
+                           bits, e.count, count_z);
+        hipLaunchKernelGGL((k_edt_tile<1, int>), tiles(ly, nz), dim3(kEdtTileThreads),
+                           lds(ly, ny) + ((long long)ny * nw <= kEdtMaskWords ? sizeof(int) * ny * nw : 0), s,
+                           (const int *)nullptr, bits, nw, e.h, e.list, e.count, nx, ny, nz, ly);
+        hipLaunchKernelGGL(k_edt_env<int>, dim3(env_grid), dim3(kThreads), 0, s, (const int *)nullptr, bits, nw, e.h, 1,
+                           ny, e.list, e.count, e.C, nx, ny, e.sv, e.sf, e.sz);
+    } else {
+        const long long lines = (long long)nx * nz;
+        hipLaunchKernelGGL(k_edt_x, dim3(line_blocks), dim3(kThreads), 0, s, vol->mask, nx, xl, e.g);
         hipLaunchKernelGGL(k_edt_clear, dim3(blocks_for(lines)), dim3(kThreads), 0, s, e.open, lines, e.count);
-        const int lg = edt_tile_log(n, nx);
-        if (lg >= 0) {
-            const dim3 tgrid((unsigned)((nx + (1 << lg) - 1) >> lg), (unsigned)(axis == 1 ? nz : ny));
-            const size_t lds = sizeof(int) * ((size_t)n << lg);
-            if (axis == 1)
-                hipLaunchKernelGGL(k_edt_tile<1>, tgrid, dim3(kThreads), lds, s, in, out, e.open, nx, ny, nz, lg);
-            else
-                hipLaunchKernelGGL(k_edt_tile<2>, tgrid, dim3(kThreads), lds, s, in, out, e.open, nx, ny, nz, lg);
-        } else if (axis == 1) {
-            hipLaunchKernelGGL(k_edt_scan<1>, grid, dim3(kThreads), 0, s, in, out, e.open, nx, ny, nz);
-        } else {
-            hipLaunchKernelGGL(k_edt_scan<2>, grid, dim3(kThreads), 0, s, in, out, e.open, nx, ny, nz);
-        }
+        hipLaunchKernelGGL(k_edt_scan<1>, grid, dim3(kThreads), 0, s, e.g, e.h, e.open, nx, ny, nz);
         hipLaunchKernelGGL(k_edt_collect, dim3(blocks_for(lines)), dim3(kThreads), 0, s, e.open, lines, e.list, e.count);
-        hipLaunchKernelGGL(k_edt_env, dim3(env_grid), dim3(kThreads), 0, s, in, out, axis, n, e.list, e.count, e.C, nx, ny,
-                           e.sv, e.sf, e.sz);
+        hipLaunchKernelGGL(k_edt_env<int>, dim3(env_grid), dim3(kThreads), 0, s, e.g, (const unsigned int *)nullptr, 0,
+                           e.h, 1, ny, e.list, e.count, e.C, nx, ny, e.sv, e.sf, e.sz);
+    }
+    // z
+    if (lz >= 0) {
+        if (ly < 0) {
+            hipLaunchKernelGGL(k_edt_clear, dim3(1), dim3(kThreads), 0, s, e.open, 0ll, e.count);
+            count_z = e.count;
+        }
+        auto pass = [&](auto *out) {
+            using Out = std::remove_pointer_t<decltype(out)>;
+            hipLaunchKernelGGL((k_edt_tile<2, Out>), tiles(lz, ny), dim3(kEdtTileThreads), lds(lz, nz), s, e.h,
+                               (const unsigned int *)nullptr, 0, out, e.list, count_z, nx, ny, nz, lz);
+            hipLaunchKernelGGL(k_edt_env<Out>, dim3(env_grid), dim3(kThreads), 0, s, e.h, (const unsigned int *)nullptr, 0,
+                               out, 2, nz, e.list, count_z, e.C, nx, ny, e.sv, e.sf, e.sz);
+        };
+        if (dist) pass(dist);
+        else pass(e.g);
+    } else {
+        const long long lines = (long long)nx * ny;
+        hipLaunchKernelGGL(k_edt_clear, dim3(blocks_for(lines)), dim3(kThreads), 0, s, e.open, lines, e.count);
+        hipLaunchKernelGGL(k_edt_scan<2>, grid, dim3(kThreads), 0, s, e.h, e.g, e.open, nx, ny, nz);
+        hipLaunchKernelGGL(k_edt_collect, dim3(blocks_for(lines)), dim3(kThreads), 0, s, e.open, lines, e.list, e.count);
+        hipLaunchKernelGGL(k_edt_env<int>, dim3(env_grid), dim3(kThreads), 0, s, e.h, (const unsigned int *)nullptr, 0, e.g,
+                           2, nz, e.list, e.count, e.C, nx, ny, e.sv, e.sf, e.sz);
+        if (dist) hipLaunchKernelGGL(k_edt_out, dim3(blocks_for(n)), dim3(kThreads), 0, s, e.g, n, dist);
     }
     HIP_TRY(hipGetLastError());
     return MC_OK;
@@ -1094,7 +1404,7 @@ SpLayout sp_layout(const mc_volume *vol, int z0, long long npore_max, hipStream_
     L.cmax = take(sizeof(unsigned long long) * 2 * nchunks);
     L.begin = take(sizeof(int) * nseg);
     L.end = take(sizeof(int) * nseg);
-    L.stats = take(sizeof(unsigned long long) * 3);
+    L.stats = take(sizeof(unsigned long long) * 4);
     L.kf = take(sizeof(long long) * npore_max);
     L.kd = take(sizeof(int) * npore_max);
     L.pos = take(sizeof(int) * npore_max);
@@ -1247,13 +1557,8 @@ int mc_pore_distance(const mc_volume *vol, double *dist, void *workspace, size_t
     if (workspace_bytes < need) return fail(MC_ENOSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
     if (too_large(vol)) return fail(MC_EINVAL, "volume too large for 32-bit squared distances");
     hipStream_t s = (hipStream_t)hip_stream;
-    const size_t nvox = (size_t)vol->nx * vol->ny * vol->nz;
     const EdtScratch e = edt_layout(vol, workspace);
-    if ((rc = enqueue_sqdist(vol, e, s))) return rc;
-    int *g = e.g;
-    hipLaunchKernelGGL(k_edt_out, dim3(blocks_for((long long)nvox)), dim3(kThreads), 0, s, g, (long long)nvox, dist);
-    HIP_TRY(hipGetLastError());
-    return MC_OK;
+    return enqueue_sqdist(vol, e, dist, s);
 }
 
 size_t mc_pore_spearman_workspace_bytes(const mc_volume *vol, int32_t z0)
@@ -1288,7 +1593,7 @@ int mc_pore_spearman(const mc_volume *vol, const int64_t *fluence, int32_t z0, d
     if (workspace_bytes < L.total) return fail(MC_ENOSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, L.total);
     char *b = (char *)workspace;
     const EdtScratch e = edt_layout(vol, b + L.edt);
-    if ((rc = enqueue_sqdist(vol, e, s))) return rc;
+    if ((rc = enqueue_sqdist(vol, e, nullptr, s))) return rc;
     const int nseg = vol->nz - z0;
     int *counts = (int *)(b + L.counts), *coff = (int *)(b + L.coff);
     unsigned long long *cmax = (unsigned long long *)(b + L.cmax);
@@ -1306,10 +1611,18 @@ int mc_pore_spearman(const mc_volume *vol, const int64_t *fluence, int32_t z0, d
     hipLaunchKernelGGL(k_compact, dim3(nchunks), dim3(kSpThreads), 0, s, vol->mask, (const long long *)fluence, e.g,
                        n_slice, z0, cps, (const int *)coff, kf, kd, pos, cmax);
     hipLaunchKernelGGL(k_chunk_max, dim3(1), dim3(kSpThreads), 0, s, (const unsigned long long *)cmax, nchunks, stats);
+    // Ranks by buckets where a workgroup takes one turn for a slice, or a few with slices for
+    // enough CUs; by sorting otherwise, and where the keys of some slice crowd few buckets.
+    // Whole calls, buckets against sort: 187 x 256 x 256 0.59 ms, 1.2; 8 x 256 x 256 0.37,
+    // 0.31; 64 x 362 x 362 1.2, 0.92; one slice of 64 x 64 0.11, 0.13.
+    const bool buckets = n_slice <= kBucketSlice && (nseg >= kBucketSlices || n_slice <= kBucketSlice / 4);
+    if (buckets)
+        hipLaunchKernelGGL(k_bucket_rank, dim3(nseg), dim3(kSpThreads), 0, s, (const long long *)kf, (const int *)begin,
+                           (const int *)end, (uint16_t *)kc, perm, rf, stats + 3);
     HIP_TRY(hipGetLastError());
-    // the pore count sizes the sorts and the key maxima fix their bit ranges: bring
-    // those three numbers to the host
-    unsigned long long st[3] = {0ull, 0ull, 0ull};
+    // the pore count sizes the sorts, the key maxima fix their bit ranges: bring those three
+    // numbers to the host, and whether the ranks by buckets left a slice
+    unsigned long long st[4] = {0ull, 0ull, 0ull, 0ull};
     {
         const hipError_t err = hipMemcpyAsync(st, stats, sizeof(st), hipMemcpyDeviceToHost, s);
         const hipError_t err2 = err == hipSuccess ? hipStreamSynchronize(s) : err;
@@ -1320,7 +1633,9 @@ int mc_pore_spearman(const mc_volume *vol, const int64_t *fluence, int32_t z0, d
         const unsigned sbits = bit_width((unsigned long long)(nseg - 1));
         const unsigned fbits = bit_width(st[1]), dbits = bit_width(st[2]);
         size_t tmp = L.tmp_bytes;
-        if (fbits < 64 && sbits + fbits <= 64) {   // no negative tally, and room for the slice number
+        if (buckets && st[3] == 0ull) {
+            // ranked
+        } else if (fbits < 64 && sbits + fbits <= 64) {   // no negative tally, and room for the slice number
             hipLaunchKernelGGL(k_compose<long long>, dim3(nseg), dim3(kSpThreads), 0, s, (const long long *)kf,
                                (const int *)begin, (const int *)end, fbits, kc);
             HIP_TRY(rocprim::radix_sort_pairs(b + L.tmp, tmp, (const unsigned long long *)kc, kc_s, (const int *)pos,
