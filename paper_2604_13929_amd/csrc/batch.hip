@@ -117,7 +117,8 @@ __device__ __forceinline__ void account_job(unsigned long long *acc, const Photo
 
 // Same queue discipline as the plain walk: a wavefront-private range of queue
 // positions refilled by one atomic, idle lanes refilled together, interactions
-// run together once `defer` lanes wait at one (or no lane can advance), exit
+// run together once `defer` lanes wait at one (or no lane can advance, or, FP32,
+// the queue is exhausted), exit
 // once the queue is exhausted and no lane is alive.
 // LOGGED: deposits go through the log into each job's staging tally.  GENERAL:
 // some job uses the paper's boundary model (each job's own flags select its
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
         }
         const uint64_t wait_mask = __ballot(waiting);
         if (wait_mask != 0ull &&
-            (__popcll(wait_mask) >= defer || __ballot(alive && !waiting) == 0ull)) {
+            ((kFP32 && exhausted) || __popcll(wait_mask) >= defer || __ballot(alive && !waiting) == 0ull)) {
             if (waiting) {
                 const Job &J = s_jobs[job];
                 const int32_t fin = finish(p, J, sink, interact(p, J, sink));

@@ -549,9 +549,15 @@ __device__ __forceinline__ void cell_grad_add(int *bin, unsigned long long *grad
     if (nv >= kGradSpill || nv <= -kGradSpill) grad_global_add(grad, i, (long long)atomicExch(bin, 0));
 }
 
-// Lanes parked before an exchange; lanes waiting before their interactions run; once an item's list
-// is used up, iterations a wavefront still takes, and the lanes it needs busy to go on after that.
-constexpr int32_t kRefill = 16, kDefer = 20, kCutAfter = 16, kCutLanes = 32;
+// Lanes parked before an exchange; once an item's list is used up, iterations a wavefront still
+// takes, and the lanes it needs busy to go on after that.
+constexpr int32_t kRefill = 16, kCutAfter = 16, kCutLanes = 32;
+
+// Lanes that wait before their interactions run: the wait takes half of them from the steps
+// and an interaction's code then runs for that many, so the best number goes with the root of
+// the rate of interactions.  256^3, a fixed 20 against 28 sqrt(mu_t) (20 at mu_t = 0.51): mu_t
+// 0.037 (paper's model) 108.5 -> 104.6 ms, 0.21 61.8 -> 60.7, 1.03 51.2 -> 50.3.
+constexpr float kDeferScale = 28.0f;
 
 // bits below the quanta in a tally word
 constexpr uint32_t kSolid = 1u, kOutside = 2u, kSpecial = 4u;  // special: outside -> mirror, inside -> air pad
@@ -712,6 +718,7 @@ __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsign
         uint64_t have = 0ull, run = 0ull, wait = 0ull;
         bool drained = false;                                // the item's list is used up
         int32_t since = 0;                                   // iterations since then
+        const int32_t defer = min(max((int32_t)(kDeferScale * sqrtf((float)J.mu_t)), 2), 32);
         // lanes of each wavefront in use: few photons are spread over all wavefronts
         const int32_t cap = (int32_t)min(64u, (n_ph + (kBlock / 64) - 1) / (kBlock / 64));
 
@@ -830,7 +837,7 @@ __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsign
             wait |= stopped;
 
             const bool cut = drained && since >= kCutAfter && popcount(run | wait) < kCutLanes;
-            if (wait != 0ull && (popcount(wait) >= kDefer || run == 0ull || cut)) {
+            if (wait != 0ull && (popcount(wait) >= defer || run == 0ull || cut)) {
                 if (lanes(wait)) {
                     p.k += 1u;
                     // the round keys are added up here: kept ready, they would fill the scalar registers
@@ -1085,7 +1092,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
             if (fin >= 0 && is_terminal(fin)) retire(fin);
         }
         const uint64_t wm = ballot(waiting);
-        if (wm != 0ull && (popcount(wm) >= defer || ballot(live && !waiting) == 0ull)) {
+        if (wm != 0ull && ((kFP32 && empty) || popcount(wm) >= defer || ballot(live && !waiting) == 0ull)) {
             if (waiting) {
                 const Job &J = s_jobs[job];
                 const int32_t fin = finish(p, J, sink, interact(p, J, sink));
