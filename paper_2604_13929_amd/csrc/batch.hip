@@ -217,7 +217,7 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
             }
             if (exhausted && q_next >= q_end && !__any(alive)) break;
         }
-        if constexpr (LOGGED) sink.tag = (uint32_t)job << kJobShift;
+        if constexpr (LOGGED) sink.tag = log_tag<true>(job);
         if (alive && !waiting) {
             const Job &J = s_jobs[job];
             const int32_t ev = advance<GENERAL>(p, J, sink);
@@ -242,12 +242,12 @@ __global__ __launch_bounds__(BLOCK) void k_walk_batch(const Job *__restrict__ jo
         // lane has filled it
         if constexpr (LOGGED) {
             if (__ballot(sink.count >= (uint32_t)kBLogK) != 0ull)
-                flush_batch_log<kFP32>(lidx, lval, s_jobs, lane,
-                                       alive ? (stage_word(s_jobs[job], p) | sink.tag) >> 4 : kBNoLine, sink.head,
-                                       sink.count);
+                flush_batch_log<kFP32, true>(lidx, lval, s_jobs, lane,
+                                             alive ? (stage_word(s_jobs[job], p) | sink.tag) >> 4 : kBNoLine,
+                                             sink.head, sink.count);
         }
     }
-    if constexpr (LOGGED) flush_batch_log<kFP32>(lidx, lval, s_jobs, lane, kBNoLine, sink.head, sink.count);
+    if constexpr (LOGGED) flush_batch_log<kFP32, true>(lidx, lval, s_jobs, lane, kBNoLine, sink.head, sink.count);
     __syncthreads();
     for (int32_t i = threadIdx.x; i < n_jobs * MC_NSCALARS; i += BLOCK) {
         const unsigned long long v = acc[i / MC_NSCALARS][i % MC_NSCALARS];

@@ -997,7 +997,8 @@ struct TailSink : BatchLoggedSink {
 constexpr int kTailBlock = 256;
 constexpr int32_t kTailRefill = 16, kTailDefer = 4;
 
-template <typename R, bool GENERAL, bool GRAD>
+// JOBS: several jobs, whose staging tallies the log's entries index with 26 bits (log_words)
+template <typename R, bool GENERAL, bool GRAD, bool JOBS>
 __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned long long *__restrict__ grad,
                                                            const BatchEsc *__restrict__ esc)
 {
@@ -1071,7 +1072,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
             empty = base + want >= total;
         }
         if (empty && ballot(live) == 0ull) break;
-        sink.tag = (uint32_t)job << kJobShift;
+        sink.tag = log_tag<JOBS>(job);
         auto retire = [&](int32_t ev) {
             unsigned long long *a = acc + (size_t)job * MC_NSCALARS;
             cell_account(a, p, ev, s_jobs[job].nz);
@@ -1102,10 +1103,11 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
         }
         // a lane logs at most one deposit per iteration
         if (ballot(sink.count >= (uint32_t)kBLogK) != 0ull)
-            flush_batch_log<kFP32>(lidx, lval, s_jobs, lane, live ? (stage_word(s_jobs[job], p) | sink.tag) >> 4 : kBNoLine,
-                                   sink.head, sink.count);
+            flush_batch_log<kFP32, JOBS>(lidx, lval, s_jobs, lane,
+                                         live ? (stage_word(s_jobs[job], p) | sink.tag) >> 4 : kBNoLine, sink.head,
+                                         sink.count);
     }
-    flush_batch_log<kFP32>(lidx, lval, s_jobs, lane, kBNoLine, sink.head, sink.count);
+    flush_batch_log<kFP32, JOBS>(lidx, lval, s_jobs, lane, kBNoLine, sink.head, sink.count);
     __syncthreads();
     for (int32_t i = threadIdx.x; i < n_jobs * MC_NSCALARS; i += kTailBlock) {
         const unsigned long long v = acc[i];
@@ -1236,7 +1238,11 @@ int enqueue_cells(const CellRun &r, const Plan &P, int rounds, int cus, const Ba
             hipLaunchKernelGGL((k_cells_walk<R, GENERAL, GRAD>), dim3(cus), dim3(walk_block<R>()), 0, s, T, r.grad, esc);
     }
     const size_t lds = (size_t)r.n_jobs * (sizeof(Job) + MC_NSCALARS * 8) + (GRAD ? (size_t)6 * r.table[0].nz * sizeof(int) : 0);
-    hipLaunchKernelGGL((k_cells_tail<R, GENERAL, GRAD>), dim3(cus * 4), dim3(kTailBlock), lds, s, T, r.grad, esc);
+    const dim3 grid(cus * 4), block(kTailBlock);
+    if constexpr (!GRAD) {
+        if (r.n_jobs > 1) hipLaunchKernelGGL((k_cells_tail<R, GENERAL, false, true>), grid, block, lds, s, T, r.grad, esc);
+    }
+    if (r.n_jobs == 1) hipLaunchKernelGGL((k_cells_tail<R, GENERAL, GRAD, false>), grid, block, lds, s, T, r.grad, esc);
     HIP_TRY(hipGetLastError());
     return MC_OK;
 }
@@ -1291,7 +1297,7 @@ bool cell_walk_fits(const CellRun &r)
     for (int32_t i = 0; i < r.n_jobs; ++i) {
         const Job &J = r.table[i];
         // the walk in cells keeps no total path to compare with a cap; the tail logs its deposits
-        if (J.path_cap != (float)kInf || J.stage == nullptr) return false;
+        if (J.path_cap != (float)kInf || J.stage == nullptr || stage_words(J) > log_words(r.n_jobs)) return false;
     }
     Plan P;
     if (!plan_of(r, &P)) return false;

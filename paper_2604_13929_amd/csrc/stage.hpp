@@ -11,10 +11,10 @@ namespace pmc {
 // entries, 16 slots per lane, issued transposed once some lane has filled its
 // slots, the run of entries in the line a photon still deposits into held back,
 // uint32 staging words in each job's own layout, planes or lines, carries of
-// wrapped words into the job's int64 tally), with the job index in the top 6 bits
-// of the 32-bit entry index, which leaves 26 bits for the word index into the
-// job's staging tally (the batch logs only when every job's staging tally is that
-// small).  A deposit of 2^31 quanta or more goes to the job's tally directly.  The
+// wrapped words into the job's int64 tally).  Where a launch carries several jobs (JOBS)
+// the job index takes the top 6 bits of the 32-bit entry index, which leaves 26 bits
+// for the word index into the job's staging tally (such a launch logs only when every
+// job's staging tally is that small); a job alone has all 32 bits for the word.  A deposit of 2^31 quanta or more goes to the job's tally directly.  The
 // log's 33 KB of LDS per 256-thread workgroup, with the job table and the per-job
 // channels, still lets three workgroups share a CU.
 constexpr int kBLogK = 16;
@@ -28,12 +28,25 @@ constexpr int kJobShift = 26;
 constexpr uint32_t kIdxMask = (1u << kJobShift) - 1u;
 constexpr uint64_t kBatchLogWords = 1ull << kJobShift;   // largest staging tally a logged batch job may have
 
+// The job's bits of an entry's index, and an entry's job and word.
+template <bool JOBS> __host__ __device__ __forceinline__ uint32_t log_tag(int32_t job) { return JOBS ? (uint32_t)job << kJobShift : 0u; }
+template <bool JOBS> __host__ __device__ __forceinline__ uint32_t log_job(uint32_t e) { return JOBS ? e >> kJobShift : 0u; }
+template <bool JOBS> __host__ __device__ __forceinline__ uint32_t log_word(uint32_t e) { return JOBS ? e & kIdxMask : e; }
+// The largest staging tally the entries of a launch of so many jobs can index.
+inline uint64_t log_words(int32_t n_jobs) { return n_jobs > 1 ? kBatchLogWords : 1ull << 32; }
+// The words of a job's staging tally.
+inline uint64_t stage_words(const Job &J)
+{
+    if (J.stage_planes) return plane_dims(J.nx, J.ny, J.nz).words;
+    return (uint64_t)J.lnx * (uint64_t)J.lny * (((uint64_t)J.nz + 3) / 4) * 16;
+}
+
 struct BatchLoggedSink {
     uint32_t *lidx;
     uint32_t *lval;
     uint32_t lane;
     uint32_t head, count;       // this lane's ring of kBLogK slots
-    uint32_t tag;               // job << kJobShift
+    uint32_t tag;               // log_tag of the job
     template <typename R> __device__ __forceinline__ void segment(const Photon<R> &, const Job &, R, bool) {}
     template <typename R> __device__ __forceinline__ void deflect(Photon<R> &, const Job &, R) {}
     template <typename R> __device__ __forceinline__ void flush(const Job &J, const Photon<R> &p, uint64_t a)
@@ -56,7 +69,7 @@ struct BatchLoggedSink {
 // Issue the wavefront's log; HOLD: the newest run of each lane's log that lies in
 // `line` (job bits included; kBNoLine: none) stays as the lane's ring.  The FP64
 // transport holds nothing.
-template <bool HOLD>
+template <bool HOLD, bool JOBS>
 __device__ __forceinline__ void flush_batch_log(uint32_t *lidx, uint32_t *lval, const Job *jobs, uint32_t lane,
                                                 uint32_t line, uint32_t &head, uint32_t &count)
 {
@@ -75,7 +88,7 @@ __device__ __forceinline__ void flush_batch_log(uint32_t *lidx, uint32_t *lval, 
             old[i] = 0u;
             if (v != 0u && (!HOLD || v < kLogHeld)) {
                 const uint32_t w = lidx[e];
-                old[i] = __hip_atomic_fetch_add(jobs[w >> kJobShift].stage + (w & kIdxMask), v, __ATOMIC_RELAXED,
+                old[i] = __hip_atomic_fetch_add(jobs[log_job<JOBS>(w)].stage + log_word<JOBS>(w), v, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -88,8 +101,8 @@ __device__ __forceinline__ void flush_batch_log(uint32_t *lidx, uint32_t *lval, 
                 if (old[i] > 0xFFFFFFFFu - v) {
                     // the word wrapped: its lost 2^32 quanta go to the voxel's int64 word
                     const uint32_t w = lidx[e];
-                    const Job &J = jobs[w >> kJobShift];
-                    __hip_atomic_fetch_add((unsigned long long *)(J.fluence + stage_voxel(J, w & kIdxMask)),
+                    const Job &J = jobs[log_job<JOBS>(w)];
+                    __hip_atomic_fetch_add((unsigned long long *)(J.fluence + stage_voxel(J, log_word<JOBS>(w))),
                                            1ull << (32 + kDepositShift), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 lval[e] = 0u;
