@@ -598,11 +598,52 @@ __device__ __forceinline__ void esc_add(const BatchEsc *esc, int32_t job, double
     __hip_atomic_fetch_add(e.rn + b, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The escape histogram of a run of one job (HIST), a workgroup's in LDS: where most photons leave by a few bins the adds to
+// their copies in memory take longer than the walk (512 x 512 x 8, 2e6 photons, bins of 8 voxels: 2.35 ms; 1.06).
+// A batch, whose workgroups go from job to job, adds to the copies.
+template <bool HIST> struct EscBins {
+    unsigned long long w[HIST ? kEscMaxBins : 1];
+    unsigned int n[HIST ? kEscMaxBins : 1];          // a workgroup's photons, fewer than 2^32
+};
+
+template <bool HIST> __device__ __forceinline__ void esc_clear(EscBins<HIST> &s)
+{
+    if (HIST)
+        for (int32_t i = threadIdx.x; i < kEscMaxBins; i += blockDim.x) {
+            s.w[i] = 0ull;
+            s.n[i] = 0u;
+        }
+}
+
+template <bool HIST>
+__device__ __forceinline__ void esc_count(EscBins<HIST> &s, const BatchEsc *esc, int32_t job, double l_void, uint32_t w)
+{
+    if (HIST) {
+        const int32_t b = escape_path_bin(l_void, esc->width, esc->nbins);
+        atomicAdd(&s.w[b], (unsigned long long)w);
+        atomicAdd(&s.n[b], 1u);
+    } else if (esc != nullptr) {
+        esc_add(esc, job, l_void, w);
+    }
+}
+
+// The workgroup's bins into one of the copies; every thread's counts are in.
+template <bool HIST> __device__ __forceinline__ void esc_flush(const EscBins<HIST> &s, const BatchEsc *esc)
+{
+    if (HIST)
+        for (int32_t i = threadIdx.x; i < esc->nbins; i += blockDim.x)
+            if (s.n[i]) {
+                const size_t b = (size_t)(blockIdx.x % kEscReplicas) * kEscMaxBins + (size_t)i;
+                __hip_atomic_fetch_add(esc->rw + b, s.w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_add(esc->rn + b, (unsigned long long)s.n[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+}
+
 // Threads of a workgroup, the one its compute unit holds: the FP64 transport's state needs more than
 // the 128 registers 16 wavefronts leave each lane.
 template <typename R> constexpr int walk_block() { return std::is_same<R, float>::value ? 1024 : 512; }
 
-template <typename R, bool GENERAL, bool GRAD>
+template <typename R, bool GENERAL, bool GRAD, bool HIST>
 __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsigned long long *__restrict__ grad,
                                                        const BatchEsc *__restrict__ esc)
 {
@@ -613,11 +654,13 @@ __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsign
     __shared__ unsigned long long acc[MC_NSCALARS];
     __shared__ uint32_t s_item, s_cursor;
     __shared__ int s_grad[GRAD ? 6 * kCell : 1];
+    __shared__ EscBins<HIST> s_esc;
     const uint32_t lane = __lane_id();
     Ctrl *c = T.ctrl;
     const uint32_t n_items = c->n_items;
     int32_t cur_job = -1;
     if (threadIdx.x < MC_NSCALARS) acc[threadIdx.x] = 0ull;
+    esc_clear(s_esc);
     uint64_t absorbed = 0ull;
 
     auto cell_word = [&](uint32_t lb) -> uint32_t { return *(const uint32_t *)__builtin_assume_aligned((const char *)tally + lb, 4); };
@@ -897,7 +940,7 @@ __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsign
                     if (iy >= J.ny) { iy = 0; ky = 0; }
                     if (iz < G.zlo || iz >= zend) {
                         cell_account(acc, p, iz < G.zlo ? EV_ESC_R : EV_ESC_T, J.nz);
-                        if (esc != nullptr) esc_add(esc, job, p.l_void, p.w);
+                        esc_count(s_esc, esc, job, p.l_void, p.w);
                         T.keys[slot] = kDead;
                     } else if ((cw & kOutside) != 0u && kx == cx && ky == cy && kz == cz) {
                         // a lateral wrap onto the cell itself
@@ -966,6 +1009,7 @@ __global__ __launch_bounds__(walk_block<R>()) void k_cells_walk(Tables T, unsign
             const unsigned long long v = acc[threadIdx.x];
             if (v) atomicAdd((unsigned long long *)&T.jobs[cur_job].scalars[threadIdx.x], v);
         }
+        esc_flush(s_esc, esc);
     }
 }
 
@@ -998,7 +1042,7 @@ constexpr int kTailBlock = 256;
 constexpr int32_t kTailRefill = 16, kTailDefer = 4;
 
 // JOBS: several jobs, whose staging tallies the log's entries index with 26 bits (log_words)
-template <typename R, bool GENERAL, bool GRAD, bool JOBS>
+template <typename R, bool GENERAL, bool GRAD, bool JOBS, bool HIST>
 __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned long long *__restrict__ grad,
                                                            const BatchEsc *__restrict__ esc)
 {
@@ -1008,6 +1052,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
     extern __shared__ unsigned long long s_dyn[];   // the jobs, their channels, the score bins
     __shared__ uint32_t s_lidx[kWaves * kBLogK * kBLogStride];
     __shared__ uint32_t s_lval[kWaves * kBLogK * kBLogStride];
+    __shared__ EscBins<HIST> s_esc;
     Ctrl *c = T.ctrl;
     const int32_t n_jobs = (int32_t)c->n_jobs;
     Job *s_jobs = (Job *)s_dyn;
@@ -1020,6 +1065,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
     uint32_t *lidx = s_lidx + (threadIdx.x >> 6) * kBLogK * kBLogStride;
     uint32_t *lval = s_lval + (threadIdx.x >> 6) * kBLogK * kBLogStride;
     for (int i = 0; i < kBLogK; ++i) lval[i * kBLogStride + lane] = 0u;
+    esc_clear(s_esc);
     TailSink<GRAD> sink;
     sink.lidx = lidx;
     sink.lval = lval;
@@ -1078,7 +1124,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
             cell_account(a, p, ev, s_jobs[job].nz);
             if (p.absorbed) atomicAdd(&a[MC_S_A], (unsigned long long)p.absorbed);
             if (p.rr) atomicAdd(&a[MC_S_RR], (unsigned long long)p.rr);
-            if (esc != nullptr && (ev == EV_ESC_R || ev == EV_ESC_T)) esc_add(esc, job, p.l_void, p.w);
+            if (ev == EV_ESC_R || ev == EV_ESC_T) esc_count(s_esc, esc, job, p.l_void, p.w);
             live = false;
         };
         if (live && !waiting) {
@@ -1109,6 +1155,7 @@ __global__ __launch_bounds__(kTailBlock) void k_cells_tail(Tables T, unsigned lo
     }
     flush_batch_log<kFP32, JOBS>(lidx, lval, s_jobs, lane, kBNoLine, sink.head, sink.count);
     __syncthreads();
+    esc_flush(s_esc, esc);
     for (int32_t i = threadIdx.x; i < n_jobs * MC_NSCALARS; i += kTailBlock) {
         const unsigned long long v = acc[i];
         if (v) atomicAdd((unsigned long long *)&s_jobs[i / MC_NSCALARS].scalars[i % MC_NSCALARS], v);
@@ -1222,7 +1269,7 @@ bool plan_of(const CellRun &r, Plan *P)
     return true;
 }
 
-template <typename R, bool GENERAL, bool GRAD>
+template <typename R, bool GENERAL, bool GRAD, bool JOBS, bool HIST>
 int enqueue_cells(const CellRun &r, const Plan &P, int rounds, int cus, const BatchEsc *esc, hipStream_t s)
 {
     const Tables &T = P.T;
@@ -1235,26 +1282,28 @@ int enqueue_cells(const CellRun &r, const Plan &P, int rounds, int cus, const Ba
         hipLaunchKernelGGL(k_cells_columns, dim3((unsigned)((P.cells + 63) / 64)), dim3(kSortThreads), 0, s, T);
         hipLaunchKernelGGL(k_cells_scatter, dim3(kSortBlocks), dim3(kSortThreads), hist, s, T, (int32_t)(k == rounds));
         if (k < rounds)
-            hipLaunchKernelGGL((k_cells_walk<R, GENERAL, GRAD>), dim3(cus), dim3(walk_block<R>()), 0, s, T, r.grad, esc);
+            hipLaunchKernelGGL((k_cells_walk<R, GENERAL, GRAD, HIST>), dim3(cus), dim3(walk_block<R>()), 0, s, T, r.grad, esc);
     }
     const size_t lds = (size_t)r.n_jobs * (sizeof(Job) + MC_NSCALARS * 8) + (GRAD ? (size_t)6 * r.table[0].nz * sizeof(int) : 0);
-    const dim3 grid(cus * 4), block(kTailBlock);
-    if constexpr (!GRAD) {
-        if (r.n_jobs > 1) hipLaunchKernelGGL((k_cells_tail<R, GENERAL, false, true>), grid, block, lds, s, T, r.grad, esc);
-    }
-    if (r.n_jobs == 1) hipLaunchKernelGGL((k_cells_tail<R, GENERAL, GRAD, false>), grid, block, lds, s, T, r.grad, esc);
+    hipLaunchKernelGGL((k_cells_tail<R, GENERAL, GRAD, JOBS, HIST>), dim3(cus * 4), dim3(kTailBlock), lds, s, T, r.grad, esc);
     HIP_TRY(hipGetLastError());
     return MC_OK;
+}
+
+template <typename R, bool GENERAL>
+int enqueue_kind(const CellRun &r, const Plan &P, int rounds, int cus, const BatchEsc *esc, hipStream_t s)
+{
+    // gradients and a histogram of its own are those of a run of one job
+    if (r.grad) return enqueue_cells<R, GENERAL, true, false, false>(r, P, rounds, cus, esc, s);
+    if (r.hist) return enqueue_cells<R, GENERAL, false, false, true>(r, P, rounds, cus, esc, s);
+    if (r.n_jobs > 1) return enqueue_cells<R, GENERAL, false, true, false>(r, P, rounds, cus, esc, s);
+    return enqueue_cells<R, GENERAL, false, false, false>(r, P, rounds, cus, esc, s);
 }
 
 template <typename R>
 int enqueue_general(const CellRun &r, const Plan &P, int rounds, int cus, const BatchEsc *esc, hipStream_t s)
 {
-    if (r.general)
-        return r.grad ? enqueue_cells<R, true, true>(r, P, rounds, cus, esc, s)
-                      : enqueue_cells<R, true, false>(r, P, rounds, cus, esc, s);
-    return r.grad ? enqueue_cells<R, false, true>(r, P, rounds, cus, esc, s)
-                  : enqueue_cells<R, false, false>(r, P, rounds, cus, esc, s);
+    return r.general ? enqueue_kind<R, true>(r, P, rounds, cus, esc, s) : enqueue_kind<R, false>(r, P, rounds, cus, esc, s);
 }
 
 }  // namespace
