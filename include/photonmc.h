@@ -77,6 +77,9 @@ extern "C" {
                                the three tables of 4 x 4-voxel planes fit (the workspace sizes allow for
                                the planes; the two layouts give identical tallies); for mc_run_batch,
                                in every job.  Implied by MC_FP64. */
+#define MC_CELLS 32         /* walk in cells (mc_run_extra_workspace_bytes) wherever this run or batch can with
+                               the workspace it is given, not where it is faster: for measurements and tests.
+                               The results are the same bit for bit */
 
 #define MC_DEPOSIT_QUANTUM 256 /* Q31 units: every tally value is a multiple of it */
 #define MC_GRAD_FIXED_BITS 20  /* mc_grad's score bins count units of 2^-20 Q31 weight x voxel */

@@ -1350,6 +1350,7 @@ bool cell_walk_fits(const CellRun &r)
     }
     Plan P;
     if (!plan_of(r, &P)) return false;
+    if (r.always) return P.slots != 0;
     const uint64_t least = std::max<uint64_t>(kMinPhotons, 2ull * di.cus * kStopPerCu);
     return r.photons >= least && P.slots >= least / 2;
 }

@@ -28,8 +28,9 @@ struct CellRun {
     const BatchEsc *hist;       // host: a single run's histogram without its copies, or NULL
     char *ws;
     size_t ws_bytes;
+    bool always;                // MC_CELLS: wherever it can, not where it is faster
 };
-// Whether this run goes faster in cells: enough photons, and scratch for enough of them at once.
+// Whether this run walks in cells: it can, and it is faster that way with this scratch.
 bool cell_walk_fits(const CellRun &r);
 // The walk alone: tallies and staging tallies zeroed and masks packed beforehand, the staging tallies
 // (which the tail logs into) added to the fluence afterwards.

@@ -23,6 +23,7 @@ MC_TIMED = 2
 MC_FP64 = 4
 MC_DIRECT_DEPOSIT = 8
 MC_LINE_STAGING = 16
+MC_CELLS = 32
 #: Q31 units per deposit quantum: each segment's deposit is rounded to a multiple of it
 ABI_VERSION = 4
 DEPOSIT_QUANTUM = 256
