@@ -199,9 +199,11 @@ size_t mc_run_workspace_bytes(const mc_volume *vol);
 /* Further workspace that makes an mc_run, mc_run_escape_histogram or mc_grad of n_photons on this
  * volume faster: given at least mc_run_workspace_bytes(vol) (mc_grad_workspace_bytes(vol)) plus this,
  * a large run walks its photons through the volume cell by cell with the tallies in LDS (1e8 photons
- * at 256^3: 0.49 s against 1.26 s), the photons under way waiting in this workspace, 72 bytes each for
- * up to 12.6e6 of them.  0 where it would not be used.  With less, fewer photons are under way at
- * once, or the run takes the path that needs none; the results are the same bit for bit. */
+ * at 256^3: 0.49 s against 1.26 s) where that is faster, which its optics, model and precision decide too.
+ * The photons under way wait in this workspace, up to 12.6e6 of 72 bytes each (16 bytes more with the
+ * paper's model and with gradients, 32 with the FP64 transport: fewer of them then).  0 where no run of
+ * this size would use it.  With less, fewer photons are under way at once, or the run takes the path that
+ * needs none; the results are the same bit for bit. */
 size_t mc_run_extra_workspace_bytes(const mc_volume *vol, uint64_t n_photons);
 
 /*

@@ -488,7 +488,7 @@ int enqueue_batch(const mc_job *jobs, const Prepared &P, char *ws, const mc_tune
     const bool timed = (flags & MC_TIMED) != 0;
     if (timed && (rc = time_begin(s))) return rc;
     const CellRun cells = {P.table.data(), n, P.total_photons, P.general, (flags & MC_FP64) != 0, nullptr,
-                           bins ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr, nullptr, P.cells, P.cells_bytes,
+                           bins ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr, nullptr, P.cells, P.cells_bytes, true,
                            (flags & MC_CELLS) != 0};
     if (!(flags & MC_LINE_STAGING) && cell_walk_fits(cells)) {
         if ((rc = cell_walk(cells, s))) return rc;

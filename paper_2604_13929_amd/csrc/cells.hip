@@ -57,9 +57,10 @@ constexpr uint32_t kMinItem = 2048, kMaxItem = 65536;   // photons of an item
 // 6 % at 4096).
 constexpr uint32_t kStopPerCu = 2560;
 constexpr uint32_t kStopPerCell = 640, kLeastPerCell = 1024;
-// The least photons of a run in rounds: the deposit log alone is as fast at 2e6 (100 x 90 x 110 voxels, 3e6
-// photons: 19.1 against 21.8 ms; 1e6: 12.6 against 10.1).
+// The least photons of a run in rounds: below, the end takes them all (faster_in_cells has what decides above it).
 constexpr uint64_t kMinPhotons = 2000000;
+// The rounds of a run are no more than this (16 000 launches, 45 ms if all are empty).
+constexpr double kMaxRounds = 4000.0;
 
 struct Grid {                              // device copy of CellDims
     int32_t ncx, ncy, ncz, ex, ey, ez, zlo;
@@ -1203,6 +1204,7 @@ uint32_t quotient_factor(int32_t e) { return e == 1 ? 0u : (uint32_t)((0x1000000
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t quads_of(const CellRun &r) { return (r.fp64 ? 6 : 4) + (r.general ? 1 : 0) + (r.grad ? 1 : 0); }
+size_t slot_bytes(const CellRun &r) { return quads_of(r) * 16 + 8; }   // with its key and its place in the list
 
 // The slots a walk of so many cells takes at most: enough for items of some 24 000 photons per cell.
 constexpr uint64_t kMaxSlots = 12ull << 20, kMinSlots = 1ull << 20;
@@ -1258,7 +1260,7 @@ bool plan_of(const CellRun &r, Plan *P)
     char *const ws = (char *)up256((size_t)r.ws);
     const size_t off = lay_tables(ws, cells, r.n_jobs, P), lost = (size_t)(ws - r.ws) + off + kSlack;
     if (r.ws_bytes <= lost) return false;
-    const size_t per = quads_of(r) * 16 + 8;
+    const size_t per = slot_bytes(r);
     uint64_t slots = std::min<uint64_t>((r.ws_bytes - lost) / per, wanted_slots(cells));
     slots = std::min<uint64_t>(slots, r.photons + 3) / 4 * 4;   // the keys are read four at a time
     P->slots = (uint32_t)slots;
@@ -1304,6 +1306,100 @@ template <typename R>
 int enqueue_general(const CellRun &r, const Plan &P, int rounds, int cus, const BatchEsc *esc, hipStream_t s)
 {
     return r.general ? enqueue_kind<R, true>(r, P, rounds, cus, esc, s) : enqueue_kind<R, false>(r, P, rounds, cus, esc, s);
+}
+
+// The path, in voxels, on which a photon's weight ends (the interactions from 1 down to the roulette's threshold, or to the
+// last bit, 10 / mu_t apart in a mask nine tenths open) or the gate does.
+double longest_path(const Job &J)
+{
+    double path = J.gate;
+    const double keep = (double)J.s_q / 4294967296.0;        // weight kept at an interaction
+    if (J.mu_t > 0.0 && keep < 1.0) {
+        const double last = J.w_th ? J.w_th / 2147483648.0 : 1.0 / 2147483648.0;
+        const double interactions = 1.0 + (keep > 0.0 ? log(last) / log(keep) : 0.0);
+        path = std::min(path, 10.0 * interactions / J.mu_t);
+    }
+    return path;
+}
+
+// Visits per voxel of path: one over the mean chord 4V/S of a cell, of whose faces those count that lie between two cells (on an
+// axis of one cell a periodic photon comes back into it).
+double chord_faces(const CellDims &d)
+{
+    return 0.5 * ((d.ncx > 1 ? 1.0 / d.ex : 0.0) + (d.ncy > 1 ? 1.0 / d.ey : 0.0) + (d.ncz > 1 ? 1.0 / d.ez : 0.0));
+}
+
+// Whether a run is faster in cells than by the log (k_walk, k_walk_batch).  What the cells save is the deposits at the memory
+// side; what they cost is a round's fixed time and a cell's (its mask in, its tally out), paid by the photons of a workgroup's
+// share and of a cell and by the steps of a visit, and the end of the run, which both walk the same way.  They save less where a
+// step does more arithmetic: interactions (mu_s), the FP64 transport, interfaces, scores.  Times of the log over those in
+// cells, at phi 0.7, mu_s 0.5, mu_a 0.01, g 0.7 but for what is said:
+//   256^3                2e6 photons 1.07, 5e6 1.45, 1e7 1.88; FP64 0.99, 1.19; paper's model 1.00, 1.23, 1.36
+//   128^3, 64^3          5e6 1.25, 1.08; FP64 128^3 1.12; paper's model 128^3 1.07
+//   512 x 512 x 8        2e6 0.94, 5e6 1.01, 1e7 1.11; FP64 0.77, 0.97, 1.04; paper's model 5e6 0.90, 2e7 1.04
+//   512 x 512 x 64       mu_s 0.036 2e6 0.90, 5e6 1.14;  64^3 0.86, 1.03;  512 x 512 x 8 1e7 0.90, 5e7 1.17
+//   40 x 256 x 40        reach 56e3: mu_s 0.5 2e6 0.96, 5e6 1.04, 2e7 1.11; mu_s 0.036 0.87, 0.89, 1.07; mu_a 0.5 0.93, 0.96, 0.94
+//   mu_s 1               2e6 0.85 to 1.0, 5e6 1.04 to 1.25
+//   mu_s 2 to 5          256^3 5e6 0.81 to 1.04, 1e7 1.03 to 1.22; 512 x 512 x 64 1.16 to 1.31; 100 x 90 x 110 0.62 to 0.97;
+//                        128^3 0.89 to 1.1; 32^3, one cell, 2e6 1.22, 5e6 1.32 to 1.48
+//   gradients            256^3 2e6 0.95, 5e6 1.13, 5e7 1.53; FP64 0.94, 1.03, 1.08; paper's model 0.88, 1.07, 1.25; 128^3 (reach
+//                        124e3) at most 0.90, FP64 0.80, paper's model 0.72; 512 x 512 x 8 5e6 0.88, 2e7 1.03, paper's model 0.91
+//   1024 x 1024 x 384    5e7 plain 1.36 (800 to 1000 photons a cell); paper's model 0.90, mu_s 0.036 2e7 1.10; gradients 0.86
+//   1 x 300 x 300        1.2 to 1.9; paper's model 0.78 to 0.94 (each step leaves the cell and comes back)
+// The log of a batch, which finds a photon's job in LDS, is slower:
+//   64 x 32^3            2e6 1.22, 2e7 1.9; FP64 1.16, 1.35; paper's model 1.20, 1.6
+//   3 x 200^3 to 256^3   2e6 1.2, 2e7 1.9; FP64 1.17, 1.6; paper's model 1.24, 1.9; mu_s 4 2e6 0.89, 6e6 1.27, 2e7 1.57
+//   64 x 64^3 to 160^3   2e6 1.08, 6e6 1.11, 2e7 1.4; FP64 0.96, 1.08, 1.27 (450, 1000, 2100 photons a cell); with the paper's
+//                        model 0.91, 1.07, 1.00;  12 x 64^3 to 128^3, mu_s 0.05 2e6 0.88, 6e6 1.37; mu_s 4 6e6 0.91, 2e7 1.35
+bool faster_in_cells(const CellRun &r, const Plan &P, int cus)
+{
+    double path = 0.0, visits = 0.0, work = 0.0, mu_s = 0.0, depth = 0.0;
+    int32_t narrow = kCell;
+    bool one_cell = true;
+    for (int32_t i = 0; i < r.n_jobs; ++i) {
+        const Job &J = r.table[i];
+        const double n = (double)J.n_photons, p = std::min(3.0 * J.nz, longest_path(J)), per = chord_faces(P.d[i]);
+        path += n * p;
+        visits += n * (1.0 + p * per);
+        work += n * J.nz;
+        mu_s += n * J.mu_s;
+        narrow = std::min(narrow, std::min(P.d[i].ex, P.d[i].ey));
+        one_cell = one_cell && per == 0.0;
+    }
+    const double photons = (double)r.photons;
+    mu_s /= photons;
+    depth = work / photons;
+    // photons of a workgroup at once, times the voxels of a visit
+    const double reach = (double)P.slots / cus * path / visits, per_cell = (double)P.slots / (double)P.cells;
+    if (r.batch) return photons >= (mu_s > 1.5 ? 4e6 : (mu_s * depth < 5.0 ? 3e6 : 0.0)) && (!r.fp64 || per_cell >= 600.0);
+    if (!one_cell && photons < (mu_s > 1.5 ? 8e6 : (mu_s > 0.75 ? 4e6 : 0.0))) return false;
+    if (mu_s > 1.5 && reach < 250e3) return false;
+    if (r.grad) {
+        const double bytes = reach * (double)slot_bytes(r) / 72.0;   // a wider photon has fewer slots and takes as much longer
+        return photons >= 3e6 && per_cell >= 2000.0 && (r.general ? depth >= 32.0 && bytes >= 360e3 : bytes >= 350e3);
+    }
+    if (r.fp64 || r.general)
+        return per_cell >= (!r.fp64 && mu_s < 0.25 ? 600.0 : 1000.0) && work >= 1.2e8 && reach >= 80e3 && narrow >= (r.general ? 4 : 8);
+    return reach >= 50e3 && work >= (mu_s * depth < 3.0 ? 2.3e8 : 5e7);
+}
+
+// The rounds to enqueue: those in which the photons are launched, each of which takes a path of three slab thicknesses, and
+// those until no more than the end are left, who fall by a factor e on 4.2 thicknesses (1075 voxels; 1075 observed).  A photon
+// visits its path over the mean chord 4V/S of a cell (chord_faces): 36 cells for 256^3, 32 observed.  A round that finds nothing
+// left costs 11 us; what a short estimate leaves the tail takes (where light diffuses slower, mu_s (1 - g) = 2 at 256^3, 1e7
+// photons, the rounds are a tenth of those it would take to the end, and all of them would be slower: 222 ms against 198).
+int rounds_of(const CellRun &r, const Plan &P, uint32_t stop_at)
+{
+    double after = 0.0, launches = 0.0;
+    const double folds = log((double)P.slots / (stop_at + 0.5 * kStopPerCell * P.cells));
+    for (int32_t i = 0; i < r.n_jobs; ++i) {
+        const Job &J = r.table[i];
+        const CellDims &d = P.d[i];
+        const double per = chord_faces(d);
+        launches += (1.0 + per * std::min(3.0 * J.nz, longest_path(J))) * (double)J.n_photons / P.slots;
+        after = std::max(after, per * std::min(4.2 * J.nz * folds, longest_path(J)));
+    }
+    return (int)std::min(kMaxRounds, 8.0 + launches + after);
 }
 
 }  // namespace
@@ -1352,7 +1448,7 @@ bool cell_walk_fits(const CellRun &r)
     if (!plan_of(r, &P)) return false;
     if (r.always) return P.slots != 0;
     const uint64_t least = std::max<uint64_t>(kMinPhotons, 2ull * di.cus * kStopPerCu);
-    return r.photons >= least && P.slots >= least / 2;
+    return r.photons >= least && P.slots >= least / 2 && faster_in_cells(r, P, di.cus);
 }
 
 int cell_walk(const CellRun &r, hipStream_t s)
@@ -1390,17 +1486,7 @@ int cell_walk(const CellRun &r, hipStream_t s)
         if ((rc = write_esc(&e, 1, P.esc, s))) return rc;
         esc = P.esc;
     }
-    // a photon's visits: a path of three slab thicknesses over the mean chord 4V/S of a cell (256^3 workload: 36,
-    // 32 observed); the photons alive fall by a factor e in 1.4 times as many rounds
-    double longest = 0.0, launches = 0.0;
-    for (int32_t i = 0; i < r.n_jobs; ++i) {
-        const CellDims &d = P.d[i];
-        const double visits = 3.0 * r.table[i].nz * 0.5 * (1.0 / d.ex + 1.0 / d.ey + 1.0 / d.ez);
-        longest = std::max(longest, visits);
-        launches += visits * (double)r.table[i].n_photons / P.slots;
-    }
-    const double decay = 1.4 * std::max(0.0, log((double)P.slots / stop_at));
-    const int rounds = (int)std::min(4000.0, 8.0 + launches + longest * decay);
+    const int rounds = rounds_of(r, P, stop_at);
     if (r.fp64) rc = enqueue_general<double>(r, P, rounds, di.cus, esc, s);
     else rc = enqueue_general<float>(r, P, rounds, di.cus, esc, s);
     if (rc) return rc;

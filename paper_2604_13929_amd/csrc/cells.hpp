@@ -28,6 +28,7 @@ struct CellRun {
     const BatchEsc *hist;       // host: a single run's histogram without its copies, or NULL
     char *ws;
     size_t ws_bytes;
+    bool batch;
     bool always;                // MC_CELLS: wherever it can, not where it is faster
 };
 // Whether this run walks in cells: it can, and it is faster that way with this scratch.

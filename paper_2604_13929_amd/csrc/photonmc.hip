@@ -1143,7 +1143,7 @@ int run_walk(const mc_volume *vol, Job J, int flags, const mc_tune &t, char *ws,
     if (logged && cells && !(flags & MC_LINE_STAGING)) {
         const BatchEsc hist = esc ? BatchEsc{esc->w, esc->n, nullptr, nullptr, esc->width, esc->nbins, 0} : BatchEsc{};
         const CellRun r = {&J, 1, J.n_photons, J.paper != 0, (flags & MC_FP64) != 0, grad_bins, nullptr,
-                           esc ? &hist : nullptr, cells, cells_bytes, (flags & MC_CELLS) != 0};
+                           esc ? &hist : nullptr, cells, cells_bytes, false, (flags & MC_CELLS) != 0};
         if (cell_walk_fits(r)) {
             const bool timed = (flags & MC_TIMED) != 0;
             if (timed && (rc = time_begin(s))) return rc;

@@ -78,14 +78,25 @@ def test_cells_wherever_they_can(dims, opt, kw):
     _same(cells, log)
 
 
-@pytest.mark.parametrize("opt,n,flags,want", [
-    (PLAIN, N, 0, True), (PLAIN, 1_999_999, 0, False), (PLAIN, N, pm.MC_LINE_STAGING, False),
-    (PLAIN, N, pm.MC_DIRECT_DEPOSIT | pm.MC_CELLS, False),
-    (pm.Optics(0.5, 0.01, 0.7, path_cap=60.0), N, pm.MC_CELLS, False)])
-def test_route(opt, n, flags, want):
-    mask = _mask(128, 128, 128)
-    extra = pm.load().mc_run_extra_workspace_bytes(ctypes.byref(pm.volume(mask)), N)
-    assert _go(mask, opt, n, flags=flags, extra=extra)[1] == want
+@pytest.mark.parametrize("dims,opt,n,kw,want", [
+    ((128, 128, 128), PLAIN, N, {}, True),
+    ((128, 128, 128), PLAIN, N, dict(bins=8), True),
+    ((128, 128, 128), PLAIN, 1_999_999, {}, False),
+    ((128, 128, 128), PLAIN, N, dict(flags=pm.MC_LINE_STAGING), False),
+    ((128, 128, 128), PLAIN, N, dict(flags=pm.MC_DIRECT_DEPOSIT | pm.MC_CELLS), False),
+    ((128, 128, 128), pm.Optics(0.5, 0.01, 0.7, path_cap=60.0), N, dict(flags=pm.MC_CELLS), False),
+    ((128, 128, 128), PLAIN, N, dict(flags=pm.MC_FP64), True),
+    ((128, 128, 128), PAPER, N, {}, True),
+    ((128, 128, 128), PLAIN, N, dict(grad=True), False),
+    ((256, 256, 256), PLAIN, 3 * N, dict(grad=True), True),
+    ((256, 256, 256), DENSE, N, {}, False),
+    ((320, 320, 8), PLAIN, N, {}, False),
+    ((1, 300, 300), PAPER, N, {}, False)])
+def test_route(dims, opt, n, kw, want):
+    mask = _mask(*dims)
+    extra = pm.load().mc_run_extra_workspace_bytes(ctypes.byref(pm.volume(mask)), max(n, N))
+    _, used = _go(mask, opt, n, extra=extra, **kw)
+    assert used == want
 
 
 @pytest.mark.parametrize("paper,fp64", [(False, False), (True, False), (True, True)])
