@@ -1013,7 +1013,10 @@ __device__ __forceinline__ void for_slice(const T *key, const U *other, int b, i
 }
 
 // Sets *skipped, and leaves the slice, where its keys would take more than kBucketCompares
-// comparisons each or a bucket holds more than kBucketKeys.
+// comparisons each or a bucket holds more than kBucketKeys.  Any slice left has all of them sorted, so
+// the others stop too: they look before each turn.  (Fluence of few photons crowds the slices near the
+// source: 256^3, 3e6 photons 1.51 ms for the whole call with the others going on to their ends,
+// 1.34 with the sort alone, now 1.19.)
 __global__ __launch_bounds__(kSpThreads) void k_bucket_rank(const long long *__restrict__ key, const int *__restrict__ begin,
                                                             const int *__restrict__ end, uint16_t *bucket, int *slot,
                                                             double *__restrict__ rank, unsigned long long *skipped)
@@ -1024,6 +1027,7 @@ __global__ __launch_bounds__(kSpThreads) void k_bucket_rank(const long long *__r
     __shared__ long long s_lo[kSpThreads / 64], s_hi[kSpThreads / 64];
     __shared__ unsigned long long s_work;
     __shared__ unsigned int s_most;
+    __shared__ unsigned long long s_skipped;
     const int b = begin[blockIdx.x], e = end[blockIdx.x], t = (int)threadIdx.x;
     if (b == e) return;
     for (int i = t; i < kBuckets; i += kSpThreads) P[i] = 0u;
@@ -1075,7 +1079,7 @@ __global__ __launch_bounds__(kSpThreads) void k_bucket_rank(const long long *__r
     atomicMax(&s_most, most);
     unsigned int run = block_inclusive_scan(sum, wsum) - sum;
     if (s_work > (unsigned long long)(kBucketCompares * (e - b)) || s_most > (unsigned int)kBucketKeys) {
-        if (t == 0) *skipped = 1ull;
+        if (t == 0) __hip_atomic_store(skipped, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     for (int i = r0; i < r1; ++i) {
@@ -1100,7 +1104,9 @@ __global__ __launch_bounds__(kSpThreads) void k_bucket_rank(const long long *__r
             else top = mid - 1;
         }
         const unsigned int next = P[u1];
+        if (t == 0) s_skipped = __hip_atomic_load(skipped, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
+        if (s_skipped) return;
         for_slice(bucket, key, b, e, [&](int i, int u, long long v) {
             if (u >= u0 && u < u1) {
                 const int at = (int)(atomicAdd(&P[u], 1u) - base);
