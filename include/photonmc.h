@@ -419,8 +419,10 @@ size_t mc_batch_extra_workspace_bytes(const mc_job *jobs, int32_t n_jobs);
  * photons, each rounded to a power of two) is used, or found by
  * mc_autotune_batch first and cached (file $PHOTONMC_TUNE_CACHE, else
  * ~/.cache/photonmc_tune.txt; MC_EINVAL if a job accumulates then, as the
- * tuning trials write to the tallies).  Errors: MC_EINVAL (a job is invalid;
- * the message names it), MC_ENOSPACE, MC_EHIP.
+ * tuning trials write to the tallies).  A batch that its workspace has walk in
+ * cells (mc_batch_extra_workspace_bytes) makes no use of a launch shape: none is
+ * looked for.  Errors: MC_EINVAL (a job is invalid; the message names it),
+ * MC_ENOSPACE, MC_EHIP.
  */
 int mc_run_batch(const mc_job *jobs, int32_t n_jobs, int flags, const mc_tune *tune, void *workspace,
                  size_t workspace_bytes, void *hip_stream);
@@ -461,7 +463,8 @@ int mc_run_batch_escape_histogram(const mc_job *jobs, int32_t n_jobs, int flags,
  * when over 1 % faster, and the result kept only if it beats the default again in
  * two more trials), store it in the tune cache and return it.
  * Synchronises the stream.  Overwrites the jobs' tallies with meaningless
- * values (MC_EINVAL if a job accumulates).
+ * values (MC_EINVAL if a job accumulates).  For a batch that this workspace has
+ * walk in cells the default shape is returned at once and nothing is stored.
  */
 int mc_autotune_batch(const mc_job *jobs, int32_t n_jobs, int flags, void *workspace, size_t workspace_bytes,
                       mc_tune *out, void *hip_stream);

@@ -454,6 +454,18 @@ int enqueue_esc_table(const Prepared &P, const mc_escape_bins *bins, char *ws, h
     return write_esc(e, n, (BatchEsc *)(ws + P.L.esc_off), s);
 }
 
+// The batch as the cell walk takes it, and whether it does.
+CellRun cell_run(const Prepared &P, int flags, const BatchEsc *esc)
+{
+    return CellRun{P.table.data(), (int32_t)P.table.size(), P.total_photons, P.general, (flags & MC_FP64) != 0, nullptr,
+                   esc, nullptr, P.cells, P.cells_bytes, true, (flags & MC_CELLS) != 0};
+}
+
+bool walks_in_cells(const Prepared &P, int flags)
+{
+    return !(flags & MC_LINE_STAGING) && cell_walk_fits(cell_run(P, flags, nullptr));
+}
+
 // The whole batched step: table, zeroed tallies, packed masks, one walk, reductions.
 // bins: per-job escape-path histograms (caller's job order, validated), or NULL.
 int enqueue_batch(const mc_job *jobs, const Prepared &P, char *ws, const mc_tune &t, int flags, hipStream_t s,
@@ -487,11 +499,8 @@ int enqueue_batch(const mc_job *jobs, const Prepared &P, char *ws, const mc_tune
     }
     const bool timed = (flags & MC_TIMED) != 0;
     if (timed && (rc = time_begin(s))) return rc;
-    const CellRun cells = {P.table.data(), n, P.total_photons, P.general, (flags & MC_FP64) != 0, nullptr,
-                           bins ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr, nullptr, P.cells, P.cells_bytes, true,
-                           (flags & MC_CELLS) != 0};
-    if (!(flags & MC_LINE_STAGING) && cell_walk_fits(cells)) {
-        if ((rc = cell_walk(cells, s))) return rc;
+    if (walks_in_cells(P, flags)) {
+        if ((rc = cell_walk(cell_run(P, flags, bins ? (const BatchEsc *)(ws + P.L.esc_off) : nullptr), s))) return rc;
     } else if ((rc = enqueue_walk_only(P, ws, t, flags, s, bins != nullptr))) {
         return rc;
     }
@@ -684,17 +693,23 @@ Prepared scaled(const Prepared &P, double fraction)
     return S;
 }
 
-int autotune_prepared(const mc_job *jobs, const Prepared &P, char *ws, int flags, hipStream_t s, mc_tune *out)
+int refuse_accumulate(const mc_job *jobs, const Prepared &P)
 {
     for (size_t i = 0; i < P.table.size(); ++i)
         if (jobs[i].accumulate)
             return fail(MC_EINVAL, "job %zu accumulates: tuning trials would add to its tallies; pass a tune", i);
+    return MC_OK;
+}
+
+int autotune_prepared(const mc_job *jobs, const Prepared &P, char *ws, int flags, hipStream_t s, mc_tune *out)
+{
+    int rc = refuse_accumulate(jobs, P);
+    if (rc) return rc;
     // trials of about 2^25 photons in total: long enough that the tail of a launch and
     // the spread between trials do not decide the shape
     const double fraction = std::min(1.0, 33554432.0 / (double)P.total_photons);
     Prepared S = scaled(P, fraction);
-    int rc = enqueue_table(S, ws, s);
-    if (rc) return rc;
+    if ((rc = enqueue_table(S, ws, s))) return rc;
     for (size_t i = 0; i < S.table.size(); ++i)
         if ((rc = pack(&jobs[S.order[i]].vol, (uint64_t *)(ws + S.L.bricks_off[S.order[i]]), s))) return rc;
     auto trial = [&](const mc_tune &t) { return enqueue_walk_only(S, ws, t, flags & MC_FP64, s); };
@@ -769,6 +784,11 @@ int mc_autotune_batch(const mc_job *jobs, int32_t n_jobs, int flags, void *works
     int rc = prepare(jobs, n_jobs, (char *)workspace, workspace_bytes, flags, &P);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
+    if (walks_in_cells(P, flags)) {
+        if ((rc = refuse_accumulate(jobs, P))) return rc;
+        *out = resolve_tune(nullptr);
+        return MC_OK;
+    }
     const std::string key = shape_key("batch", P, flags);
     if ((rc = autotune_prepared(jobs, P, (char *)workspace, flags, s, out))) return rc;
     cache_put(key, *out);
@@ -787,8 +807,8 @@ int run_batch(const mc_job *jobs, int32_t n_jobs, int flags, const mc_tune *tune
     if (rc) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
     mc_tune t;
-    if (tune) {
-        t = resolve_tune(tune);
+    if (tune || walks_in_cells(P, flags)) {
+        t = resolve_tune(tune);                  // the cells have a shape of their own: there is nothing to find
     } else {
         const std::string key = shape_key("batch", P, flags);
         if (!cache_get(key, &t)) {

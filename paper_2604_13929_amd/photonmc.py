@@ -575,7 +575,8 @@ class Batch:
 def run_batch(jobs: list[BatchJob], tune: Tune | None = None, fp64: bool = False, timed: bool = False,
               accumulate_into: Batch | None = None, escape_bins: list | None = None,
               line_staging: bool = False) -> Batch:
-    """mc_run_batch on the current stream; tune None: the cached (or autotuned) launch shape.
+    """mc_run_batch on the current stream; tune None: the cached (or autotuned) launch shape,
+    of which a batch that walks in cells makes no use.
     escape_bins: one (bin_width, nbins) or None per job: mc_run_batch_escape_histogram,
     which also bins each job's escaping photons by in-pore path into
     batch.results[i].escape_hist_w / escape_hist_n.  line_staging: MC_LINE_STAGING."""
