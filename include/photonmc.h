@@ -175,9 +175,10 @@ typedef struct {
 } mc_optics;
 
 /* Launch shape of the persistent walk.  Any value <= 0 selects the default.
- * Results do not depend on it.  With fewer photons than the shape has lanes, every
- * wavefront takes its even share of them and no more lanes than that.  The walk in
- * cells (mc_run_extra_workspace_bytes) has a shape of its own. */
+ * Results do not depend on it.  No wavefront takes more photons at once than its even
+ * share; with fewer photons than the shape has lanes it uses no more lanes than that
+ * share, and no more than an eighth of those wait at an interaction.  The walk in cells
+ * (mc_run_extra_workspace_bytes) has a shape of its own. */
 typedef struct {
     int32_t block;         /* threads per workgroup: 64, 128, 256, 512 */
     int32_t waves_per_cu;  /* resident waves per compute unit the grid is sized for */

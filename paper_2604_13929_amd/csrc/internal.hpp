@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "photonmc.h"
 #include "walk.hpp"
 
@@ -82,11 +84,20 @@ int check_tune(const mc_tune &t);
 // What a walk of so many wavefronts does with a tune for so many photons.  With fewer photons than
 // lanes every wavefront takes its even share and no more lanes than that: a wavefront of one photon
 // steps in 0.7 us, one of 64 in 1.3 to 3 us, and the run lasts as long as its longest photon.  Few
-// lanes also wait less for each other's interactions.
+// lanes also wait less for each other's interactions; a full wavefront waits for as many as the tune says.
 struct WalkShape {
     int32_t cap, chunk, refill, defer;
 };
-WalkShape walk_shape(const mc_tune &t, uint64_t waves, uint64_t photons);
+inline WalkShape walk_shape(const mc_tune &t, uint64_t waves, uint64_t photons)
+{
+    const uint64_t share = std::max<uint64_t>(1, (photons + waves - 1) / waves);
+    WalkShape s;
+    s.cap = (int32_t)std::min<uint64_t>(64, share);
+    s.chunk = (int32_t)std::min<uint64_t>((uint64_t)t.chunk, share);
+    s.refill = std::min(t.refill, s.cap);
+    s.defer = s.cap < 64 ? std::min(t.defer, std::max(1, s.cap / 8)) : t.defer;
+    return s;
+}
 
 // asynchronous building blocks on a stream
 int fill(int64_t *p, uint64_t n, hipStream_t s);

@@ -970,17 +970,6 @@ mc_tune resolve_tune(const mc_tune *t, int32_t defer_default)
     return r;
 }
 
-WalkShape walk_shape(const mc_tune &t, uint64_t waves, uint64_t photons)
-{
-    const uint64_t share = std::max<uint64_t>(1, (photons + waves - 1) / waves);
-    WalkShape s;
-    s.cap = (int32_t)std::min<uint64_t>(64, share);
-    s.chunk = (int32_t)std::min<uint64_t>((uint64_t)t.chunk, share);
-    s.refill = std::min(t.refill, s.cap);
-    s.defer = std::min(t.defer, std::max(1, s.cap / 8));
-    return s;
-}
-
 int check_tune(const mc_tune &t)
 {
     if (t.block != 64 && t.block != 128 && t.block != 256 && t.block != 512)
