@@ -334,6 +334,12 @@ def _extra_workspace(need: int, extra: int, device) -> torch.Tensor:
     return workspace(need, device)
 
 
+def _kept(ws: torch.Tensor, need: int) -> torch.Tensor | None:
+    """What a result keeps of its call's workspace: not one with up to 0.9 GB of extra scratch, which
+    torch's allocator hands out again on the stream of the call, behind its work."""
+    return ws if ws.numel() <= max(need, 256) else None
+
+
 def workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
@@ -384,7 +390,7 @@ def run(mask: torch.Tensor, optics: Optics, n_photons: int, seed: int, photon_be
                                          ws.data_ptr(), ws.numel(), tref, width, nbins,
                                          res.escape_hist_w.data_ptr(), res.escape_hist_n.data_ptr(), _stream(dev)),
                "mc_run_escape_histogram")
-    res._ws = ws  # keep the workspace alive with the queued work
+    res._ws = _kept(ws, need)  # keep the workspace alive with the queued work
     if timed:
         ms = ctypes.c_float(0.0)
         _check(L.mc_walk_elapsed_ms(ctypes.byref(ms)), "mc_walk_elapsed_ms")
@@ -541,6 +547,7 @@ class Batch:
         nbytes = L.mc_batch_workspace_bytes(ctypes.byref(arr), len(jobs))
         if nbytes == 0:
             raise McError(-1, "mc_batch_workspace_bytes", "invalid batch")
+        self.need = nbytes
         self.ws = _extra_workspace(nbytes, L.mc_batch_extra_workspace_bytes(ctypes.byref(arr), len(jobs)), dev)
 
     def attach_escape_bins(self, escape_bins: list, accumulate_into: "Batch | None" = None):
@@ -593,6 +600,7 @@ def run_batch(jobs: list[BatchJob], tune: Tune | None = None, fp64: bool = False
         _check(L.mc_run_batch_escape_histogram(ctypes.byref(b.c_jobs), len(jobs), flags, tref,
                                                ctypes.byref(b.c_bins), b.ws.data_ptr(), b.ws.numel(),
                                                _stream(b.device)), "mc_run_batch_escape_histogram")
+    b.ws = _kept(b.ws, b.need)
     if timed:
         ms = ctypes.c_float(0.0)
         _check(L.mc_walk_elapsed_ms(ctypes.byref(ms)), "mc_walk_elapsed_ms")
@@ -676,7 +684,7 @@ def grad(mask: torch.Tensor, optics: Optics, n_photons: int, seed: int, photon_b
                      summary.data_ptr(), depth.data_ptr(), ws.data_ptr(), ws.numel(),
                      ctypes.byref(t) if t is not None else None, _stream(dev)), "mc_grad")
     res = GradResult(run_, bins, jac, summary, depth)
-    res._ws = ws
+    res._ws = _kept(ws, need)
     if timed:
         ms = ctypes.c_float(0.0)
         _check(L.mc_walk_elapsed_ms(ctypes.byref(ms)), "mc_walk_elapsed_ms")
