@@ -26,10 +26,10 @@ if ROOT not in sys.path:
 METRIC = "photon-steps/sec and photons/sec at 256^3 phi=0.70; batched vs plain"
 HBM_PEAK_GBS = 8000.0
 BYTES_PER_STEP = 8  # one int64 track-length deposit per photon-step
-# the device sources the walk kernel is built from; counter summaries under profiles/ record their hash
-SOURCES = ["include/photonmc.h", "paper_2604_13929_amd/csrc/batch.hip", "paper_2604_13929_amd/csrc/internal.hpp",
-           "paper_2604_13929_amd/csrc/philox.hpp", "paper_2604_13929_amd/csrc/photonmc.hip",
-           "paper_2604_13929_amd/csrc/walk.hpp"]
+# the device sources the walk kernels are built from; counter summaries under profiles/ record their hash
+SOURCES = ["include/photonmc.h"] + ["paper_2604_13929_amd/csrc/" + f for f in
+                                    ("batch.hip", "cells.hip", "cells.hpp", "internal.hpp", "philox.hpp", "photonmc.hip",
+                                     "score.hpp", "stage.hpp", "walk.hpp")]
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "k_walk_plain_256cube_phi070_traffic.json")
 FORMS_RECORD = os.path.join(ROOT, "profiles", "k_walk_batch_grad_counters.json")
 
