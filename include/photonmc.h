@@ -76,7 +76,8 @@ extern "C" {
 #define MC_LINE_STAGING 16  /* stage the logged deposits in one table of 2 x 2 x 4-voxel lines even where
                                the three tables of 4 x 4-voxel planes fit (the workspace sizes allow for
                                the planes; the two layouts give identical tallies); for mc_run_batch,
-                               in every job.  Implied by MC_FP64. */
+                               in every job.  FP64 walks stage that way by themselves.  The flag also
+                               keeps a run or batch out of the cells */
 #define MC_CELLS 32         /* walk in cells (mc_run_extra_workspace_bytes) wherever this run or batch can with
                                the workspace it is given, not where it is faster: for measurements and tests.
                                The results are the same bit for bit */

@@ -14,9 +14,9 @@
 // Once too few photons are alive to fill the chip this way, the rounds end and k_cells_tail
 // walks the rest to their ends with the deposit log.  The number of rounds enqueued is an
 // estimate made on the host, so that nothing waits for the device and the sequence can be
-// captured: rounds after the end return at once, and what a short estimate leaves undone the tail
-// does.  A photon's own history, the integer tallies and so every result are those of k_walk, bit
-// for bit.
+// captured: rounds after the end return at once, and what a short estimate (or one of more than
+// kMaxRounds, 1.3e9 photons at 256^3) leaves undone the tail does.  A photon's own history, the
+// integer tallies and so every result are those of k_walk, bit for bit.
 // Measured on the 256^3 workload of 1e8 photons: 491 ms (1.98e11 steps/s) against 1259 ms.  Within
 // a round the walk is bound by its VALU (busy 91 % of the cycles its wavefronts are resident, which
 // is 84 % of the round): 86 wave-instructions per iteration, about 48 of 64 lanes stepping.
@@ -72,7 +72,7 @@ struct Ctrl {
     unsigned long long next_id;            // next queue position to launch
     unsigned long long total;              // queue positions
     uint32_t n_items, item_cursor;
-    uint32_t alive, done, arrived;
+    uint32_t alive, done;
     uint32_t stop_at;                      // rounds end once no more photons than this (and kStopPerCell a cell) are worth one
     unsigned long long tail_next;
     uint32_t n_jobs, n_cells, slots, walkers;   // walkers: workgroups of the walk
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kSortThreads) void k_cells_scatter(Tables T, int32_
     __syncthreads();
     const uint32_t alive = s_alive;
     if (blockIdx.x == 0) {
-        // photons per item: about four items per workgroup of the walk
+        // photons per item: a workgroup's even share, so about one full item each, and what is left of each cell
         const uint32_t W = min(max(alive / c->walkers, kMinItem), kMaxItem);
         // the items by size, largest first: each workgroup of the walk takes the next one when it is
         // done with its last, and the short ones even out the end
