@@ -12,6 +12,7 @@ already resident in HBM.  Prints one JSON line.
 from __future__ import annotations
 
 import argparse
+import ctypes
 import json
 import math
 import os
@@ -31,6 +32,7 @@ SOURCES = ["include/photonmc.h"] + ["paper_2604_13929_amd/csrc/" + f for f in
                                     ("batch.hip", "cells.hip", "cells.hpp", "internal.hpp", "philox.hpp", "photonmc.hip",
                                      "score.hpp", "stage.hpp", "walk.hpp")]
 TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "k_walk_plain_256cube_phi070_traffic.json")
+CELLS_RECORD = os.path.join(ROOT, "profiles", "cells_walk_256cube_phi070_counters.json")
 FORMS_RECORD = os.path.join(ROOT, "profiles", "k_walk_batch_grad_counters.json")
 
 
@@ -85,12 +87,52 @@ def plain_roofs(rec: dict, photons: int, photon_steps: int, walk_ms: float):
     return traffic, atomic, valu
 
 
+def cells_used(call, need: int, extra: int) -> bool:
+    """Whether a run walks in cells: call(ws) makes it with a workspace of need + extra bytes, the
+    extra ones marked, and only the walk in cells writes there."""
+    import torch
+
+    ws = torch.full((need + extra,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    call(ws)
+    torch.cuda.synchronize()
+    return bool((ws[need:] != 0xA5).any())
+
+
+def cells_roofline(photons: int, photon_steps: int, walk_ms: float):
+    """Roofline of the plain workload's walk in cells: photon-steps per second against what the VALU
+    would allow if it were busy all of the walk's time with the instructions the committed counter
+    record counts for k_cells_walk (4 cycles per wave64 instruction on each of 1024 SIMDs, at the clock
+    the record's cycles and times give); peak and traffic are None when the kernel sources changed
+    since the counters were taken."""
+    achieved = photon_steps / (walk_ms * 1e-3)
+    out = {"bound": "valu", "kernel": "k_cells_walk", "achieved": achieved, "peak": None, "unit": "photon-steps/s",
+           "frac": None, "traffic": None, "algorithmic_bytes_per_step": BYTES_PER_STEP,
+           "algorithmic_GB_per_s": achieved * BYTES_PER_STEP / 1e9}
+    try:
+        with open(CELLS_RECORD) as fh:
+            rec = json.load(fh)
+    except (OSError, ValueError):
+        return out
+    if rec.get("source_sha256") != source_sha256():
+        return out
+    w = rec["k_cells_walk"]
+    scale = photons / rec["photons"]
+    simd_cycles = w["SQ_ACTIVE_INST_VALU"] * scale * 4 / 1024
+    out["peak"] = photon_steps / (simd_cycles / rec["clock_hz"])
+    out["frac"] = achieved / out["peak"]
+    out["traffic"] = rec["traffic_bytes_per_run"] * scale
+    out["valu_instructions_per_step"] = w["SQ_INSTS_VALU"] / rec["photon_steps"]
+    out["thread_utilisation"] = w["thread_utilisation"]
+    out["source"] = os.path.relpath(CELLS_RECORD, ROOT)
+    return out
+
+
 def walk_roofline(form: str, photon_steps: int, walk_ms: float):
     """Roofline of the batched or differentiated walk launch just timed: the algorithmic
-    HBM rate (8 B per photon-step) against 8 TB/s, and the memory-side atomic request
-    rate (requests per launch from the committed counter record of the same workload)
-    against the measured ceiling for those requests; None for the latter when the kernel
-    sources changed since the counters were taken."""
+    HBM rate (8 B per photon-step) against 8 TB/s, and, where the walk was by the deposit
+    log, the memory-side atomic request rate (requests per launch from the committed counter
+    record of the same workload) against the measured ceiling for those requests; None for
+    the latter when the kernel sources changed since the counters were taken."""
     achieved = photon_steps * BYTES_PER_STEP / (walk_ms * 1e-3) / 1e9
     out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
            "algorithmic_bytes_per_step": BYTES_PER_STEP, "atomic_request_roof": None}
@@ -112,6 +154,18 @@ def walk_roofline(form: str, photon_steps: int, walk_ms: float):
     return out
 
 
+def form_roofline(form: str, in_cells: bool, photon_steps: int, walk_ms: float):
+    """The roofline of a batched or differentiated walk with the kernel that ran: walk_roofline for the
+    deposit log; the cells are bound by the VALU, and no counters of these workloads are on record."""
+    if in_cells:
+        achieved = photon_steps / (walk_ms * 1e-3)
+        return {"bound": "valu", "kernel": "k_cells_walk", "achieved": achieved, "peak": None, "unit": "photon-steps/s",
+                "frac": None, "traffic": None, "algorithmic_bytes_per_step": BYTES_PER_STEP,
+                "algorithmic_GB_per_s": achieved * BYTES_PER_STEP / 1e9}
+    return {**walk_roofline(form, photon_steps, walk_ms),
+            "kernel": {"batched": "k_walk_batch", "differentiated": "k_walk"}[form]}
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -127,8 +181,8 @@ def cpu_model():
 
 
 def batched_leg(args, seed):
-    """The uneven 64-job batch: one persistent launch (autotuned, with the reductions)
-    against the same 64 jobs as sequential plain runs (mc_run + mc_reduce each)."""
+    """The uneven 64-job batch: one batched walk (autotuned where a launch shape applies, with the
+    reductions) against the same 64 jobs as sequential plain runs (mc_run + mc_reduce each)."""
     import torch
 
     from paper_2604_13929_amd import inputs
@@ -147,10 +201,19 @@ def batched_leg(args, seed):
     n_total = sum(j.n_photons for j in jobs)
     vox = sum(j.mask.numel() for j in jobs)
     log(f"batch: 64 masks ({vox / 1e6:.0f} Mvoxels, {n_total / 1e6:.0f} M photons) built in {time.time() - t0:.1f}s")
+    L = pm.load()
+    probe = pm.Batch(jobs)
+    need = L.mc_batch_workspace_bytes(ctypes.byref(probe.c_jobs), len(jobs))
+    dflt = pm.Tune().c()
+    in_cells = cells_used(lambda ws: pm._check(L.mc_run_batch(ctypes.byref(probe.c_jobs), len(jobs), 0, ctypes.byref(dflt),
+                                                              ws.data_ptr(), ws.numel(), pm._stream(dev)), "mc_run_batch"),
+                          need, probe.ws.numel() - need)
+    del probe
     t0 = time.perf_counter()
-    tuned = pm.autotune_batch(jobs)  # timed trials on a scaled-down copy; also stored in the tune cache
+    # timed trials on a scaled-down copy, stored in the tune cache; none where the batch walks in cells
+    tuned = pm.autotune_batch(jobs)
     t_tune = time.perf_counter() - t0
-    log(f"batch autotune: {tuned} in {t_tune:.1f}s")
+    log(f"batch walks {'in cells' if in_cells else 'by the log'}, autotune: {tuned} in {t_tune:.1f}s")
     b = pm.run_batch(jobs)           # warm-up, with the cached shape
     torch.cuda.synchronize()
     log("batch warm-up done")
@@ -205,11 +268,12 @@ def batched_leg(args, seed):
             "ms": t_b * 1e3, "walk_ms": min(walk), "photon_steps_per_s": steps / t_b, "photons_per_s": n_total / t_b,
             "sequential_plain_ms": t_seq * 1e3, "sequential_photon_steps_per_s": steps / t_seq,
             "speedup_vs_sequential": t_seq / t_b, "jobs_bitwise_equal_to_plain": identical,
-            "autotuned_shape": {"block": tuned.block, "waves_per_cu": tuned.waves_per_cu, "chunk": tuned.chunk,
-                                "refill": tuned.refill, "defer": tuned.defer, "tuning_s": t_tune},
+            "walk": "cells" if in_cells else "log", "tuning_s": t_tune,
+            "autotuned_shape": None if in_cells else {"block": tuned.block, "waves_per_cu": tuned.waves_per_cu,
+                                                      "chunk": tuned.chunk, "refill": tuned.refill, "defer": tuned.defer},
             "walk_ms_default_shape": walk_default,
             "walk_ms_with_escape_histograms": walk_esc, "escape_histograms_consistent": esc_ok,
-            "roofline": walk_roofline("batched", steps, min(walk))}
+            "roofline": form_roofline("batched", in_cells, steps, min(walk))}
 
 
 def batch_oracle_check(jobs, specs, seed, m=100_000):
@@ -652,6 +716,12 @@ def grad_leg(args, seed, mask):
     jac = g.jac.cpu().numpy()
     t_lr = time.perf_counter() - t0
     steps = int(g.run.scalars[pm.SCALARS.index("steps")].item())
+    L, vol, c_opt = pm.load(), pm.volume(mask), base.c()
+    in_cells = cells_used(lambda ws: pm._check(L.mc_grad(ctypes.byref(vol), ctypes.byref(c_opt), 0, n, seed, 0, 0,
+                                                         g.run.fluence.data_ptr(), g.run.scalars.data_ptr(), g.bins.data_ptr(),
+                                                         None, None, None, ws.data_ptr(), ws.numel(), None,
+                                                         pm._stream(mask.device)), "mc_grad"),
+                          L.mc_grad_workspace_bytes(ctypes.byref(vol)), L.mc_run_extra_workspace_bytes(ctypes.byref(vol), n))
     log(f"grad: {t_lr * 1e3:.0f} ms (walk {g.walk_ms:.0f} ms)")
     B, h = 8, 1e-3
     chunk = n // B
@@ -682,7 +752,7 @@ def grad_leg(args, seed, mask):
             "workload": "plain workload, d<Phi>_3D and d<Phi>_1D (and dPhi(z)) wrt solid mu_s, mu_a, g",
             "ms": t_lr * 1e3, "walk_ms": g.walk_ms, "photon_steps_per_s": steps / t_lr, "photons_per_s": n / t_lr,
             "check_vs_crn_fd": res, "fd_relative_step": h, "subranges": B,
-            "columns": ["d_phi3d", "d_phi1d"], "roofline": walk_roofline("differentiated", steps, g.walk_ms)}
+            "columns": ["d_phi3d", "d_phi1d"], "roofline": form_roofline("differentiated", in_cells, steps, g.walk_ms)}
 
 
 def main():
@@ -837,6 +907,11 @@ def main():
     photons_per_s = n * args.steps / t_el
     walk_avg_ms = float(np.mean(walk_ms))
     achieved_gbs = steps_per_run * BYTES_PER_STEP / (walk_avg_ms * 1e-3) / 1e9
+    L, vol, c_opt, c_tune = pm.load(), pm.volume(mask), opt.c(), tune.c()
+    in_cells = cells_used(lambda ws: pm._check(L.mc_run(ctypes.byref(vol), ctypes.byref(c_opt), 0, n, seed, 0, 0,
+                                                        res.fluence.data_ptr(), res.scalars.data_ptr(), ws.data_ptr(),
+                                                        ws.numel(), ctypes.byref(c_tune), pm._stream(dev)), "mc_run"),
+                          L.mc_run_workspace_bytes(ctypes.byref(vol)), L.mc_run_extra_workspace_bytes(ctypes.byref(vol), n))
     del res, outs
     # the same workload once through the FP64 reference transport (outside the timed steps)
     r64 = pm.run(mask, opt, n, seed, timed=True, fp64=True, tune=tune)
@@ -878,7 +953,9 @@ def main():
                                              "steps_per_photon", "Pw_void_gtL", "mean_void_path")},
     }
 
-    tr = recorded_traffic(n)
+    tr = None if in_cells else recorded_traffic(n)
+    if in_cells:
+        line["roofline"] = cells_roofline(n, steps_per_run, walk_avg_ms)
     if tr is not None:
         rec, _ = tr
         traffic, line["atomic_request_roof"], line["valu_roof"] = plain_roofs(rec, n, steps_per_run, walk_avg_ms)
